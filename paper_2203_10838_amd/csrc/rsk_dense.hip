@@ -35,10 +35,7 @@ __global__ void rownorm2_dense_kernel(const T* __restrict__ A, int64_t m, int64_
   const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
   const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
   for (int64_t i = wave; i < m; i += nwaves) {
-    const T* rowp = A + i * ld;
-    double s = 0.0;
-    for (int64_t j = lane; j < n; j += 64) { const double v = (double)rowp[j]; s += v * v; }
-    s = wave_sum(s);
+    const double s = row_sq(A + i * ld, n, lane);
     if (lane == 0) r2[i] = (T)s;
   }
 }

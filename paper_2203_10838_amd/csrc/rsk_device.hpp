@@ -190,4 +190,48 @@ struct __attribute__((aligned(sizeof(T) * N))) Vec {
   T v[N];
 };
 
+// Sum of squares of p[0 .. n) in double by one wave (every lane gets it): 16-byte loads, kRowSqLoads
+// of them in flight a lane (8 KB a wave). Bound by HBM: 100000 x 20000 float32 in 1300 us, 6.1 TB/s
+// (2180 us, 3.7 TB/s, with one 4-byte load a lane at a time).
+// The loads ask only for the element's own alignment, which is what gfx950 needs for a global
+// 16-byte load, so rows of any length and pitch take the same path. Fixed order: lane l adds
+// the chunks l, l + 64, ... into one sum per element position, then the positions, then the lanes.
+constexpr int kRowSqLoads = 8;
+template <typename T>
+__device__ __forceinline__ double row_sq(const T* __restrict__ p, int64_t n, int lane) {
+  constexpr int V = 16 / (int)sizeof(T);
+  typedef T vt __attribute__((ext_vector_type(V), aligned(sizeof(T))));
+  double s[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) s[e] = 0.0;
+  const int64_t nch = n / V;
+  for (int64_t q0 = 0; q0 < nch; q0 += 64 * kRowSqLoads) {
+    vt v[kRowSqLoads];
+    // the last block's lanes past the row load its last chunk and are not added
+#pragma unroll
+    for (int u = 0; u < kRowSqLoads; ++u) {
+      const int64_t q = q0 + 64 * u + lane;
+      v[u] = *reinterpret_cast<const vt*>(p + (q < nch ? q : nch - 1) * V);
+    }
+#pragma unroll
+    for (int u = 0; u < kRowSqLoads; ++u) {
+      const bool in = q0 + 64 * u + lane < nch;
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        const double x = in ? (double)v[u][e] : 0.0;
+        s[e] += x * x;
+      }
+    }
+  }
+  const int64_t j = nch * V + lane;  // at most V - 1 elements after the last whole chunk
+  if (j < n) {
+    const double x = (double)p[j];
+    s[0] += x * x;
+  }
+  double t = s[0];
+#pragma unroll
+  for (int e = 1; e < V; ++e) t += s[e];
+  return wave_sum(t);
+}
+
 }  // namespace rsk
