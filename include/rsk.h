@@ -331,7 +331,11 @@ int32_t rsk_workspace_size_csr(const rsk_csr *A, const rsk_params *p, size_t *by
  * float64 steps of at most 64 KB that kernel 4 takes, 4; for float32, 3 for
  * 88 <= eta <= 800 unless kernel 2's whole next-step tile fits its LDS
  * prefetch (one row pass of at most 9 float4 slots a thread), else 2, where
- * the register tile applies; else 1. The
+ * the register tile applies; else 1. float32 rows that are not whole 16-byte
+ * chunks (n or ld not a multiple of 4, or A off a 16-byte boundary): 4 where
+ * it applies, else the register tile by the same rules for n >= 17 (its form
+ * for such rows is the library's choice only: an explicit 2 or 3 asks for
+ * aligned rows), else 1. The
  * kernels sum in different orders (results agree to rounding); each gives
  * bitwise reproducible x* and x (y_out: see rsk_params; kernel 4 applies y in
  * a fixed order as well).

@@ -120,6 +120,12 @@ using rsk::kOneHopWords;
 // is faster (20000 columns, eta = 96 ... 256: 4-7% shorter steps)
 constexpr int kRtTwoGroupMinEta = 88, kRtTwoGroupMaxEta = 800;
 constexpr int kRtPfBytes = 147456;
+// Ragged float32 rows (rows_ragged) take the one-workgroup kernel 4 wherever it applies, else the
+// register tile from this length on (its slices then span more than one workgroup), else the
+// general kernel. Measured, us a step, general kernel / register tile / kernel 4: n = 65, eta = 1
+// 3.4 / 4.1 / 3.3; 503, 16: 8.7 / 4.8 / 2.5; 2047, 4: 10.0 / 4.9 / 2.1; 9, 128: 5.4 / 7.8 / -; 187, 128:
+// 8.7 / 5.0 / -; 2047, 334: 15.9 / 5.8 / -; 9999, 334: 39.5 / 9.2 / -; 19999, 1000: 143 / 20.6 / -.
+constexpr int kRtRagMinN = 17;
 
 size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 size_t elem_size(int32_t dt) { return dt == RSK_F64 ? 8 : 4; }
@@ -156,6 +162,7 @@ int32_t check_params(const rsk_params* p, int64_t m) {
 struct DensePlan {
   int kernel;  // 1 general, 2 register tile, 4 one workgroup with the step in registers
   int nt, rp, cpl, rg;
+  bool rag;    // register tile on rows that are not whole 16-byte chunks
   int vec, G, two_hop, tile_cache, wq_max, lpr, W;
   int64_t nchunks;
   size_t offP, offC, offM, offU, bytes;
@@ -187,11 +194,19 @@ int32_t check_dense(const rsk_dense* A) {
   return RSK_OK;
 }
 
+// float32 rows that are not whole 16-byte chunks on 16-byte boundaries
+bool rows_ragged(const rsk_dense* A) {
+  return (A->n % 4) != 0 || (A->ld % 4) != 0 || (((uintptr_t)A->val) % 16) != 0;
+}
+
 // float32 register-tile plan: one 1024-thread workgroup per CU (512 for eta > 768), eta <= 1024,
-// rg row groups of G/rg column slices, each slice at most 5*rg units of 16 floats. Returns false,
-// with *pl unchanged, if it does not apply.
+// rg row groups of G/rg column slices, each slice at most 5*rg units of 16 floats. Rows that are not
+// whole 16-byte chunks (n or ld not a multiple of 4, or the base) are taken where the choice of the
+// kernel is the library's (kernel = 0). Returns false, with *pl unchanged, if it does not apply.
 bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* pl) {
-  if (A->dtype != RSK_F32 || (A->n % 4) != 0 || (A->ld % 4) != 0 || (((uintptr_t)A->val) % 16) != 0) return false;
+  if (A->dtype != RSK_F32) return false;
+  const bool rag = rows_ragged(A);
+  if (rag && (p->kernel != 0 || A->n < kRtRagMinN)) return false;
   const int64_t nchunks = (A->n + 3) / 4;
   const int64_t nunits = (nchunks + 3) / 4;
   const int cus = device_cus();
@@ -209,7 +224,7 @@ bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* p
   const int etaR = (p->eta + rg - 1) / rg;
   const int rpp = nt / (4 * rg);  // group rows of one pass
   const int rp = (etaR + rpp - 1) / rpp;
-  if (rsk::dense_rt_max_grid(nt, rp, cpl, rg) < G) return false;
+  if (rsk::dense_rt_max_grid(nt, rp, cpl, rg, rag) < G) return false;
   int two_hop = ((int64_t)C * etaR) > rsk::kRtOneHopWords;
   // each wave reduces at most kRtOwnMax rows per step
   const int own = rsk::kRtOwnMax * (nt / 64);
@@ -217,7 +232,7 @@ bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* p
   if (two_hop && (etaR + C - 1) / C > own) return false;
   // the plan is written only once the kernel applies: a caller falls back to the general
   // kernel with *pl as it was
-  pl->kernel = 2; pl->nt = nt; pl->rp = rp; pl->cpl = cpl; pl->rg = rg;
+  pl->kernel = 2; pl->nt = nt; pl->rp = rp; pl->cpl = cpl; pl->rg = rg; pl->rag = rag;
   pl->vec = 4; pl->W = 1; pl->nchunks = nchunks; pl->G = G;
   pl->wq_max = 4 * rg * cpl; pl->lpr = 4; pl->tile_cache = 0;
   pl->two_hop = two_hop;
@@ -253,11 +268,11 @@ int32_t plan_dense(const rsk_dense* A, const rsk_params* p, DensePlan* pl) {
 template <typename T>
 int32_t plan_dense_fixed(const rsk_dense* A, const rsk_params* p, DensePlan* pl) {
   const size_t s = sizeof(T);
-  pl->kernel = 1; pl->nt = pl->rp = pl->cpl = 0; pl->rg = 1;
+  pl->kernel = 1; pl->nt = pl->rp = pl->cpl = 0; pl->rg = 1; pl->rag = false;
   // one workgroup, the step in registers: asked for, or by default for a small system whose step
-  // is bound by latency (a float64 step of at most kSmallStepBytes)
+  // is bound by latency (a float64 or ragged float32 step of at most kSmallStepBytes)
   const int cpt = rsk::dense_small_cpt(A->n, p->eta);
-  if (p->kernel == 4 || (p->kernel == 0 && p->grid <= 1 && cpt && A->dtype == RSK_F64 &&
+  if (p->kernel == 4 || (p->kernel == 0 && p->grid <= 1 && cpt && (A->dtype == RSK_F64 || rows_ragged(A)) &&
                          (double)p->eta * (double)A->n * (double)s <= kSmallStepBytes)) {
     if (!cpt || p->grid > 1) return RSK_ERR_UNSUPPORTED;
     pl->kernel = 4; pl->nt = 256; pl->cpl = cpt; pl->vec = 1; pl->W = (int)(s / 4);
@@ -361,7 +376,7 @@ int32_t solve_dense_t(const rsk_dense* A, const void* b, const rsk_params* p, vo
   if (rsk::launch_zero_words((u64*)w, pl.bytes / sizeof(u64), stream) != hipSuccess) return RSK_ERR_HIP;
   if (zero_status && rsk::launch_zero_status(p->status_dev, stream) != hipSuccess) return RSK_ERR_HIP;
   if (pl.kernel == 2) {
-    if (rsk::launch_dense_rt(*reinterpret_cast<rsk::DenseArgs<float>*>(&a), pl.nt, pl.rp, pl.cpl, pl.rg, stream) !=
+    if (rsk::launch_dense_rt(*reinterpret_cast<rsk::DenseArgs<float>*>(&a), pl.nt, pl.rp, pl.cpl, pl.rg, pl.rag, stream) !=
         hipSuccess)
       return RSK_ERR_HIP;
     return RSK_OK;

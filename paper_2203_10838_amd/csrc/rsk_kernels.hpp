@@ -339,8 +339,9 @@ hipError_t launch_persistent(const void* fn, dim3 grid, dim3 block, void** args,
 
 // float32 register-tile kernel: NT threads, RP row passes of NT/(4 RG) rows, CPL float4 chunks
 // per lane, RG row groups (1 or 2) of G/RG column slices
-int dense_rt_max_grid(int nt, int rp, int cpl, int rg);
-hipError_t launch_dense_rt(DenseArgs<float>& a, int nt, int rp, int cpl, int rg, hipStream_t stream);
+// rag: rows of any length and pitch (else n and ld multiples of 4 and A on a 16-byte boundary)
+int dense_rt_max_grid(int nt, int rp, int cpl, int rg, bool rag);
+hipError_t launch_dense_rt(DenseArgs<float>& a, int nt, int rp, int cpl, int rg, bool rag, hipStream_t stream);
 // kRtOwnMax: rows of a step one wave of the register-tile kernel reduces
 constexpr int kRtMaxEta = 1024, kRtMaxCPL = 5, kRtOwnMax = 4;
 
