@@ -120,6 +120,9 @@ using rsk::kOneHopWords;
 // is faster (20000 columns, eta = 96 ... 256: 4-7% shorter steps)
 constexpr int kRtTwoGroupMinEta = 88, kRtTwoGroupMaxEta = 800;
 constexpr int kRtPfBytes = 147456;
+// (256 workgroups of 20000 columns, us a step without / with LO: eta = 16 7.4 / 6.9, 64 6.7 / 6.5, 96
+// 7.2 / 7.2, 128 7.6 / 7.7)
+constexpr int kRtSmallEta = 95;
 // Ragged float32 rows (rows_ragged) take the one-workgroup kernel 4 wherever it applies, else the
 // register tile from this length on (its slices then span more than one workgroup), else the
 // general kernel. Measured, us a step, general kernel / register tile / kernel 4: n = 65, eta = 1
@@ -162,7 +165,7 @@ int32_t check_params(const rsk_params* p, int64_t m) {
 struct DensePlan {
   int kernel;  // 1 general, 2 register tile, 4 one workgroup with the step in registers
   int nt, rp, cpl, rg;
-  bool rag;    // register tile on rows that are not whole 16-byte chunks
+  bool rag, lo;  // register tile: rows that are not whole 16-byte chunks; the form for small steps
   int vec, G, two_hop, tile_cache, wq_max, lpr, W;
   int64_t nchunks;
   size_t offP, offC, offM, offU, bytes;
@@ -211,7 +214,17 @@ bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* p
   const int64_t nunits = (nchunks + 3) / 4;
   const int cus = device_cus();
   int G = p->grid > 0 ? p->grid : cus;
-  if (G > nunits * rg) G = (int)(nunits * rg);
+  if (G > nunits * rg) {
+    G = (int)(nunits * rg);
+    // fewer units than workgroups: a power of two of them (the owners' polls are then whole waves and
+    // the slices whole XCD rounds). Measured, us a step, nunits / the power of two below: 63 / 32
+    // workgroups, eta = 64 5.7 / 4.8, eta = 16 4.8 / 4.9; 94 / 64, eta = 334 6.7 / 6.2; 209 / 128, eta = 16
+    // 5.4 / 4.8, eta = 334 7.9 / 6.5, eta = 1000 10.3 / 9.9; below 32 the units themselves: 19 / 16,
+    // eta = 150 4.6 / 5.1
+    // (fewer than 16 rows: the units too; 63 / 32, eta = 1 4.1 / 4.6, eta = 8 4.5 / 4.7)
+    if (p->grid <= 0 && rg == 1 && G >= 32 && p->eta >= 16)
+      while (G & (G - 1)) G &= G - 1;
+  }
   if (rg > 1 && G >= 16) G -= G % 8;  // whole XCD rounds keep a slice's groups on one XCD
   G -= G % rg;
   if (G > 256) return false;
@@ -224,15 +237,20 @@ bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* p
   const int etaR = (p->eta + rg - 1) / rg;
   const int rpp = nt / (4 * rg);  // group rows of one pass
   const int rp = (etaR + rpp - 1) / rpp;
-  if (rsk::dense_rt_max_grid(nt, rp, cpl, rg, rag) < G) return false;
-  int two_hop = ((int64_t)C * etaR) > rsk::kRtOneHopWords;
+  // one hop while every wave reduces at most one row of few partials (each row more costs a
+  // serial poll, sum and division)
+  int two_hop = (int64_t)C * etaR > rsk::kRtSoloOneHopWords || etaR > nt / 64;
   // each wave reduces at most kRtOwnMax rows per step
   const int own = rsk::kRtOwnMax * (nt / 64);
   if (!two_hop && etaR > own) two_hop = 1;
   if (two_hop && (etaR + C - 1) / C > own) return false;
+  // small steps (LO): several rows a wave, or at most kRtSmallEta rows, the whole next tile in LDS
+  const bool lo = rg == 1 && nt == 1024 && rp * cpl <= kRtPfBytes / (nt * 16) &&
+                  (p->eta <= kRtSmallEta || (two_hop && (etaR + C - 1) / C > nt / 64));
+  if (rsk::dense_rt_max_grid(nt, rp, cpl, rg, rag, lo) < G) return false;
   // the plan is written only once the kernel applies: a caller falls back to the general
   // kernel with *pl as it was
-  pl->kernel = 2; pl->nt = nt; pl->rp = rp; pl->cpl = cpl; pl->rg = rg; pl->rag = rag;
+  pl->kernel = 2; pl->nt = nt; pl->rp = rp; pl->cpl = cpl; pl->rg = rg; pl->rag = rag; pl->lo = lo;
   pl->vec = 4; pl->W = 1; pl->nchunks = nchunks; pl->G = G;
   pl->wq_max = 4 * rg * cpl; pl->lpr = 4; pl->tile_cache = 0;
   pl->two_hop = two_hop;
@@ -268,7 +286,7 @@ int32_t plan_dense(const rsk_dense* A, const rsk_params* p, DensePlan* pl) {
 template <typename T>
 int32_t plan_dense_fixed(const rsk_dense* A, const rsk_params* p, DensePlan* pl) {
   const size_t s = sizeof(T);
-  pl->kernel = 1; pl->nt = pl->rp = pl->cpl = 0; pl->rg = 1; pl->rag = false;
+  pl->kernel = 1; pl->nt = pl->rp = pl->cpl = 0; pl->rg = 1; pl->rag = pl->lo = false;
   // one workgroup, the step in registers: asked for, or by default for a small system whose step
   // is bound by latency (a float64 or ragged float32 step of at most kSmallStepBytes)
   const int cpt = rsk::dense_small_cpt(A->n, p->eta);
@@ -376,7 +394,7 @@ int32_t solve_dense_t(const rsk_dense* A, const void* b, const rsk_params* p, vo
   if (rsk::launch_zero_words((u64*)w, pl.bytes / sizeof(u64), stream) != hipSuccess) return RSK_ERR_HIP;
   if (zero_status && rsk::launch_zero_status(p->status_dev, stream) != hipSuccess) return RSK_ERR_HIP;
   if (pl.kernel == 2) {
-    if (rsk::launch_dense_rt(*reinterpret_cast<rsk::DenseArgs<float>*>(&a), pl.nt, pl.rp, pl.cpl, pl.rg, pl.rag, stream) !=
+    if (rsk::launch_dense_rt(*reinterpret_cast<rsk::DenseArgs<float>*>(&a), pl.nt, pl.rp, pl.cpl, pl.rg, pl.rag, pl.lo, stream) !=
         hipSuccess)
       return RSK_ERR_HIP;
     return RSK_OK;

@@ -82,7 +82,7 @@ __device__ __forceinline__ float4 load_unaligned(const float* p) {
 
 }  // namespace
 
-template <int NT, int RP, int CPL, int RG, bool RAG>
+template <int NT, int RP, int CPL, int RG, bool RAG, bool LO>
 __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
   constexpr int kRtThreads = NT;
   constexpr int kRtWaves = NT / 64;
@@ -116,6 +116,13 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
   // eta = 16, 64 and 256 steps 7-10% shorter). With slots left to load from HBM the prefetch
   // needs the whole exchange to hide it, and is issued right after the dots.
   constexpr bool kPfAfterHop1 = kHbmSlots == 0;
+  // LO: the steps whose length is a chain of latencies (many rows a wave, or few rows). A wave that
+  // reduces several rows fetched their b and norms in branches, an index and a value round trip a
+  // row: 3 us of a step of 64 rows. With LO lane j fetches row j of its wave, all rows at once, from
+  // indices loaded a step earlier (n = 500, eta = 64: 8.1 -> 4.5 us a step together with the second
+  // hop; eta = 256 5.1 -> 4.7; n = 20000, eta = 16 7.4 -> 6.9). Other steps hide the branch's wait
+  // and keep it: n = 10000, eta = 256 7.2 us a step against 7.5 with LO.
+  static_assert(!LO || (RG == 1 && kHbmSlots == 0), "lane-owned rows: one group, the whole next tile in LDS");
   __shared__ float4 pf[NPF > 0 ? NPF * NT : 1];
   __shared__ int nrow[PL > 0 ? PL * kRtRowsPerPass : 1];  // rows of the passes holding prefetched slots
 
@@ -182,7 +189,11 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
   // the first is checked: a load inside a branch is waited for at once, one
   // round trip each.
   int rowi[RP];
-  float ob[kOwnMax], orn[kOwnMax];
+  // b and ||a||^2 of the wave's rows j (rows ot0 + wave + kRtWaves * j of the group): with LO held by
+  // lane j, the row's index loaded a step earlier still; else all by lane 0
+  constexpr int kOwnRegs = LO ? 1 : kOwnMax;
+  float ob[kOwnRegs], orn[kOwnRegs];
+  int oi = 0;
   int lerr = 0;
   auto fetch_rows = [&](int64_t k, int (&ri_out)[RP], int& err) {
     const int32_t* tk = a.idx + k * (int64_t)eta;
@@ -213,21 +224,36 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
       }
     }
   };
+  const int oj = ot0 + wave + kRtWaves * (lane < kOwnMax ? lane : 0);
+  auto fetch_owned_index = [&](int64_t k) {
+    if constexpr (LO)
+      if (ot0 + wave < ot1) oi = a.idx[(k < a.K ? k : a.K - 1) * (int64_t)eta + (oj < ot1 ? hr0 + oj : 0)];
+  };
   auto fetch_owned = [&](int64_t k) {
-    const int32_t* tk = a.idx + k * (int64_t)eta + hr0;
+    if constexpr (LO) {
+      if (ot0 + wave >= ot1) return;
+      // step k's indices are in oi; step k + 1's follow
+      const int i = oi >= 0 && (int64_t)oi < a.m ? oi : 0;
+      ob[0] = a.b[i];
+      orn[0] = weighted_rn(a.r2, a.row_w, i);
+      fetch_owned_index(k + 1);
+    } else {
+      const int32_t* tk = a.idx + k * (int64_t)eta + hr0;
 #pragma unroll
-    for (int j = 0; j < kOwnMax; ++j) {
-      const int t = ot0 + wave + kRtWaves * j;
-      ob[j] = 0.f;
-      orn[j] = 1.f;
-      if (lane == 0 && t < ot1) {
-        const int i = tk[t];
-        if (i >= 0 && (int64_t)i < a.m) { ob[j] = a.b[i]; orn[j] = weighted_rn(a.r2, a.row_w, i); }
+      for (int j = 0; j < kOwnMax; ++j) {
+        const int t = ot0 + wave + kRtWaves * j;
+        ob[j] = 0.f;
+        orn[j] = 1.f;
+        if (lane == 0 && t < ot1) {
+          const int i = tk[t];
+          if (i >= 0 && (int64_t)i < a.m) { ob[j] = a.b[i]; orn[j] = weighted_rn(a.r2, a.row_w, i); }
+        }
       }
     }
   };
   if (a.K > 0) {
     fetch_rows(0, rowi, lerr);
+    fetch_owned_index(0);
     fetch_owned(0);
   }
   int64_t k_done = 0;
@@ -344,11 +370,11 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
 #pragma unroll
         for (int i = 0; i < kMaxG / 64; ++i) sum += v[i];
         sum = wave_sum(sum);
-        if (lane == 0) {
+        if (lane == (LO ? j : 0)) {
           float c;
-          const float rn = orn[j];
+          const float rn = orn[LO ? 0 : j];
           if (rn == 0.f) { c = NAN; set_status(a.status, ST_ZERO_ROW); }
-          else c = (ak / (float)eta) * (sum - ob[j]) / rn;
+          else c = (ak / (float)eta) * (sum - ob[LO ? 0 : j]) / rn;
           if (a.two_hop) {
             put_tagged(&a.xC[hr0 + t], c, tag);
           } else {
@@ -561,13 +587,25 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
 template <bool RAG>
 void* rt_kernel(int nt, int rp, int cpl, int rg) {
 #define RT_CASE(N, R, C, H) \
-  if (nt == N && rp == R && cpl == C && rg == H) return reinterpret_cast<void*>(&rska_dense_rt<N, R, C, H, RAG>);
+  if (nt == N && rp == R && cpl == C && rg == H) return reinterpret_cast<void*>(&rska_dense_rt<N, R, C, H, RAG, false>);
 #define RT_CPL(N, R, H) RT_CASE(N, R, 1, H) RT_CASE(N, R, 2, H) RT_CASE(N, R, 3, H) RT_CASE(N, R, 4, H) RT_CASE(N, R, 5, H)
   RT_CPL(1024, 1, 1) RT_CPL(1024, 2, 1) RT_CPL(1024, 3, 1)
   RT_CPL(512, 7, 1) RT_CPL(512, 8, 1)
   RT_CPL(1024, 1, 2) RT_CPL(1024, 2, 2) RT_CPL(1024, 3, 2)
   RT_CPL(512, 7, 2) RT_CPL(512, 8, 2)
 #undef RT_CPL
+#undef RT_CASE
+  return nullptr;
+}
+
+// The LO kernels: 1024 threads, one row group, tiles of at most 9 slots a thread.
+template <bool RAG>
+void* rt_kernel_lo(int rp, int cpl) {
+#define RT_CASE(R, C) \
+  if (rp == R && cpl == C) return reinterpret_cast<void*>(&rska_dense_rt<1024, R, C, 1, RAG, true>);
+  RT_CASE(1, 1) RT_CASE(1, 2) RT_CASE(1, 3) RT_CASE(1, 4) RT_CASE(1, 5)
+  RT_CASE(2, 1) RT_CASE(2, 2) RT_CASE(2, 3) RT_CASE(2, 4)
+  RT_CASE(3, 1) RT_CASE(3, 2) RT_CASE(3, 3)
 #undef RT_CASE
   return nullptr;
 }

@@ -101,10 +101,13 @@ __host__ __device__ inline int64_t onehop_lds_elems(int64_t G, int64_t eta) {
 // thread of a 256-thread workgroup, then per-row sums in LDS).
 constexpr int64_t kOneHopWords = 4096;
 
-// The register-tile kernel gathers all C*eta partials in one hop only up to this many words per
-// step: above it the flat poll costs more than the two-hop exchange (measured on 8000- and
-// 20000-column slices over 256 workgroups).
+// The batched register tile gathers all C*eta partials in one hop only up to this many words per
+// step: above it the flat poll costs more than the two-hop exchange.
 constexpr int64_t kRtOneHopWords = 2048;
+// The single-system register tile: one hop up to this many words and one row a wave. Measured, us a
+// step, one hop / two hops: 32 workgroups, 16 rows 4.4 / 4.7, 24 rows 4.9 / 4.6, 64 rows 6.8 / 4.7; 63
+// workgroups, 16 rows 4.7 / 5.3; 128 workgroups, 8 rows 4.8 / 4.8, 16 rows 5.5 / 4.8; 256, 8 rows 5.5 / 5.2.
+constexpr int64_t kRtSoloOneHopWords = 1024;
 
 // One CSR persistent solve (single workgroup).
 constexpr int kCsrMaxEta = 4096;  // rows per step of the CSR kernel
@@ -340,8 +343,9 @@ hipError_t launch_persistent(const void* fn, dim3 grid, dim3 block, void** args,
 // float32 register-tile kernel: NT threads, RP row passes of NT/(4 RG) rows, CPL float4 chunks
 // per lane, RG row groups (1 or 2) of G/RG column slices
 // rag: rows of any length and pitch (else n and ld multiples of 4 and A on a 16-byte boundary)
-int dense_rt_max_grid(int nt, int rp, int cpl, int rg, bool rag);
-hipError_t launch_dense_rt(DenseArgs<float>& a, int nt, int rp, int cpl, int rg, bool rag, hipStream_t stream);
+// lo: the form for small steps
+int dense_rt_max_grid(int nt, int rp, int cpl, int rg, bool rag, bool lo);
+hipError_t launch_dense_rt(DenseArgs<float>& a, int nt, int rp, int cpl, int rg, bool rag, bool lo, hipStream_t stream);
 // kRtOwnMax: rows of a step one wave of the register-tile kernel reduces
 constexpr int kRtMaxEta = 1024, kRtMaxCPL = 5, kRtOwnMax = 4;
 
