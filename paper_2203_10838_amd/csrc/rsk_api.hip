@@ -781,9 +781,12 @@ int32_t check_bsk(const rsk_dense* A, const rsk_params* p) {
   return RSK_OK;
 }
 
-// The bsk workspace: per-step relaxations [K], unit row norms [m], then the RSKA solve's own.
+// The bsk workspace: per-step relaxations [K], unit row norms [m], the partial Gram matrices of one
+// chunk of steps, then the RSKA solve's own.
 struct BskLayout {
-  size_t offAlpha, offOnes, offSolve, bytes;
+  size_t offAlpha, offOnes, offGram, offSolve, bytes;
+  int64_t chunk, wspan;
+  int splits;
   rsk_params p2;
 };
 
@@ -791,7 +794,9 @@ template <typename T>
 int32_t bsk_layout(const rsk_dense* A, const rsk_params* p, BskLayout* L) {
   L->offAlpha = 0;
   L->offOnes = align256((size_t)(p->K > 0 ? p->K : 1) * sizeof(T));
-  L->offSolve = L->offOnes + align256((size_t)A->m * sizeof(T));
+  L->offGram = L->offOnes + align256((size_t)A->m * sizeof(T));
+  rsk::bsk_gram_plan(A->n, p->K, sizeof(T) == 8, &L->chunk, &L->splits, &L->wspan);
+  L->offSolve = L->offGram + (size_t)L->chunk * L->splits * rsk::kBskMaxEta * rsk::kBskMaxEta * sizeof(double);
   L->p2 = *p;
   L->p2.alpha = 1.0;
   L->p2.alpha_k = (const void*)1;  // placeholders with the solve's validity; set at launch
@@ -823,6 +828,10 @@ int32_t bsk_solve_t(const rsk_dense* A, const void* b, const rsk_params* p, void
   a.alpha_k = (T*)(w + L.offAlpha);
   a.ones = (T*)(w + L.offOnes);
   a.norm2_hist = norm2;
+  a.gram = (double*)(w + L.offGram);
+  a.chunk = L.chunk;
+  a.splits = L.splits;
+  a.wspan = L.wspan;
   a.status = p->status_dev;
   if (rsk::launch_zero_status(p->status_dev, s) != hipSuccess) return RSK_ERR_HIP;
   if (rsk::launch_bsk_norms<T>(a, s) != hipSuccess) return RSK_ERR_HIP;

@@ -443,6 +443,18 @@ hipError_t launch_power(const LbArgs<T>& a, int64_t iters, T* v, double* est, hi
 // written as the relaxations alpha_k = eta w / ||A_tau_k||_2^2 of an RSKA solve with unit row norms.
 constexpr int kBskMaxEta = 64;
 constexpr int kBskThreads = 256;
+// Gram matrices are formed for `chunk` steps at a time (32 KB each). float64 forms them over `splits`
+// column splits, about kBskBlocks workgroups a launch; a split's four waves take wspan columns each,
+// and the split follows from n alone, so a resumed run gets the same bits. float32 has one split.
+constexpr int64_t kBskBlocks = 2048, kBskSpan = 640;
+constexpr int kBskGroup = 32;  // wspan is a multiple of this
+inline void bsk_gram_plan(int64_t n, int64_t K, bool split, int64_t* chunk, int* splits, int64_t* wspan) {
+  const int64_t q = ((n + 3) / 4 + kBskGroup - 1) / kBskGroup * kBskGroup;
+  *wspan = q < kBskSpan ? q : kBskSpan;
+  *splits = split ? (int)((n + 4 * *wspan - 1) / (4 * *wspan)) : 1;
+  const int64_t most = kBskBlocks / *splits > 0 ? kBskBlocks / *splits : 1;
+  *chunk = K < 1 ? 1 : K < most ? K : most;
+}
 template <typename T>
 struct BskArgs {
   const T* A;
@@ -454,6 +466,9 @@ struct BskArgs {
   T* alpha_k;             // out: K relaxations
   T* ones;                // out: m unit row norms
   double* norm2_hist;     // nullable, K entries: ||A_tau_k||_2^2
+  double* gram;           // chunk * splits partial Gram matrices (kBskMaxEta^2 doubles each)
+  int64_t chunk, wspan;   // bsk_gram_plan
+  int splits;
   int* status;
 };
 template <typename T>

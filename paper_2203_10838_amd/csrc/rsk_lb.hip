@@ -268,219 +268,6 @@ __global__ __launch_bounds__(1024) void pw_start(T* v, int64_t n) {
 }
 
 // ---------------------------------------------------------------------------
-// Block sparse Kaczmarz, eq. (bsk) of Sec. 1.1 (eta <= kBskMaxEta rows a step):
-//   x*_{k+1} = x*_k - w A_tau^T (A_tau x_k - b_tau) / ||A_tau||_2^2,  x_{k+1} = S_lambda(x*_{k+1}).
-// ||A_tau_k||_2^2 depends on the step's rows only, not on x, so bsk_norms computes it for
-// every step up front (persistent workgroups, one step at a time): the Gram matrix
-// A_tau A_tau^T over LDS tiles of the rows, then its largest eigenvalue to rounding
-// (Householder tridiagonalisation in double, Sturm-count multisection). It writes the
-// per-step relaxation alpha_k = eta w / ||A_tau_k||_2^2, with which the RSKA step with unit
-// row norms, (alpha_k / eta) sum_t (<a_t, x> - b_t) a_t, is the block step of eq. (bsk);
-// the iteration itself then runs in the persistent RSKA kernels.
-// ---------------------------------------------------------------------------
-
-constexpr int kBskTile = 64;  // columns per LDS tile
-constexpr int kBskQ = kBskMaxEta / (kBskThreads / 64);  // columns of the Gram matrix a lane updates
-
-struct BskEig {
-  double Gm[kBskMaxEta][kBskMaxEta + 1];
-  double vs[kBskMaxEta], ws[kBskMaxEta], dd[kBskMaxEta], ee[kBskMaxEta];
-  double pr[kBskThreads / 64][kBskMaxEta];
-  double bnd[2][kBskThreads / 64];
-};
-
-__device__ __forceinline__ double wave_max_d(double v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v = fmax(v, __shfl_xor(v, off));
-  return v;
-}
-
-// Largest eigenvalue of the symmetric eta x eta matrix in L.Gm (destroyed), by the whole
-// workgroup. Lane i of wave q owns row i and columns kBskQ q .. kBskQ q + kBskQ - 1; the
-// scalars every wave needs are computed by every wave alike from the same data.
-__device__ double gram_lambda_max(BskEig& L, int eta) {
-  const int tid = threadIdx.x, i = tid & 63, q = tid >> 6, j0 = q * kBskQ;
-  if (tid < kBskMaxEta) { L.vs[tid] = 0.0; L.ws[tid] = 0.0; L.ee[tid] = 0.0; L.dd[tid] = 0.0; }
-  __syncthreads();
-  // Householder reduction to tridiagonal form: H = I - beta v v^T on rows/columns k+1..
-  for (int k = 0; k + 2 < eta; ++k) {
-    const bool own = i > k && i < eta;
-    const double xi = own ? L.Gm[i][k] : 0.0;
-    const double nx2 = lane_sum(xi * xi, 64);
-    double alpha = 0.0;
-    if (nx2 > 0.0) {
-      const double x0 = L.Gm[k + 1][k];
-      alpha = x0 > 0.0 ? -sqrt(nx2) : sqrt(nx2);
-      const double vi = own ? (i == k + 1 ? xi - alpha : xi) : 0.0;
-      const double beta = 2.0 / lane_sum(vi * vi, 64);
-      if (q == 0) L.vs[i] = vi;
-      __syncthreads();
-      double pp = 0.0;
-#pragma unroll 4
-      for (int c = 0; c < kBskQ; ++c) {
-        const int j = j0 + c;
-        pp += (own && j > k && j < eta) ? L.Gm[i][j] * L.vs[j] : 0.0;
-      }
-      L.pr[q][i] = pp;
-      __syncthreads();
-      double pi = 0.0;
-#pragma unroll
-      for (int r = 0; r < kBskThreads / 64; ++r) pi += L.pr[r][i];
-      pi *= beta;
-      const double pv = lane_sum(own ? pi * vi : 0.0, 64);
-      const double wi = pi - 0.5 * beta * pv * vi;
-      if (q == 0) L.ws[i] = wi;
-      __syncthreads();
-#pragma unroll 4
-      for (int c = 0; c < kBskQ; ++c) {
-        const int j = j0 + c;
-        if (own && j > k && j < eta) L.Gm[i][j] -= vi * L.ws[j] + wi * L.vs[j];
-      }
-      __syncthreads();
-    }
-    if (tid == 0) {
-      L.dd[k] = L.Gm[k][k];
-      L.ee[k] = alpha;
-    }
-  }
-  __syncthreads();
-  if (tid == 0) {
-    if (eta >= 2) {
-      L.dd[eta - 2] = L.Gm[eta - 2][eta - 2];
-      L.ee[eta - 2] = L.Gm[eta - 1][eta - 2];
-    }
-    L.dd[eta - 1] = L.Gm[eta - 1][eta - 1];
-  }
-  __syncthreads();
-  // count(s) = #eigenvalues < s = #negative pivots of T - s I; thread l tests shift s_l.
-  const double di = i < eta ? L.dd[i] : -INFINITY;
-  const double ri = i < eta ? fabs(i > 0 ? L.ee[i - 1] : 0.0) + fabs(i + 1 < eta ? L.ee[i] : 0.0) : 0.0;
-  double lo = wave_max_d(di), hi = wave_max_d(i < eta ? di + ri : -INFINITY);
-  const double e2max = wave_max_d(i < eta ? L.ee[i] * L.ee[i] : 0.0);
-  const double pivmin = 2.2250738585072014e-308 * fmax(1.0, e2max);
-  constexpr double kParts = kBskThreads + 1;
-  for (int round = 0; round < 10 && hi > lo; ++round) {
-    const double width = hi - lo;
-    const double sg = lo + width * (double)(tid + 1) / kParts;
-    int cnt = 0;
-    double qv = L.dd[0] - sg;
-    if (fabs(qv) < pivmin) qv = -pivmin;
-    cnt += qv < 0.0;
-    for (int t = 1; t < eta; ++t) {
-      qv = (L.dd[t] - sg) - L.ee[t - 1] * L.ee[t - 1] / qv;
-      if (fabs(qv) < pivmin) qv = -pivmin;
-      cnt += qv < 0.0;
-    }
-    // shifts at or below lambda_max have cnt < eta; they are a prefix of the threads
-    const unsigned long long below = __ballot(cnt < eta);
-    if (i == 0) L.bnd[round & 1][q] = (double)__popcll(below);
-    __syncthreads();
-    int nb = 0;
-#pragma unroll
-    for (int r = 0; r < kBskThreads / 64; ++r) nb += (int)L.bnd[round & 1][r];
-    if (nb == 0) {
-      hi = lo + width / kParts;
-    } else {
-      const double nlo = lo + width * (double)nb / kParts;
-      hi = nb == kBskThreads ? hi : lo + width * (double)(nb + 1) / kParts;
-      lo = nlo;
-    }
-  }
-  return 0.5 * (lo + hi);
-}
-
-template <typename T>
-__global__ __launch_bounds__(kBskThreads) void bsk_norms(const T* __restrict__ A, int64_t m, int64_t n, int64_t ld,
-                                                         const int* __restrict__ tau0, int eta, int64_t K, double w,
-                                                         T* __restrict__ alpha_k, double* __restrict__ norm2,
-                                                         int* status) {
-  __shared__ T tile[kBskMaxEta][kBskTile + 1];
-  __shared__ int rows[kBskMaxEta];
-  __shared__ BskEig L;
-  const int tid = threadIdx.x;
-  const int eta4 = (eta + 3) & ~3;
-  const int bi = tid / 16, bj = tid % 16;  // this thread's 4x4 block of the Gram matrix
-  const bool gb = 4 * bi < eta && 4 * bj < eta;
-  constexpr int kLoads = kBskMaxEta * kBskTile / kBskThreads;  // tile elements a thread loads
-  for (int64_t k = blockIdx.x; k < K; k += gridDim.x) {
-    if (tid < kBskMaxEta) {
-      int r = -1;
-      if (tid < eta) {
-        r = tau0[k * eta + tid];
-        if (r < 0 || r >= m) {
-          set_status(status, ST_INDEX);
-          r = -1;
-        }
-      }
-      rows[tid] = r;
-    }
-    __syncthreads();
-    T acc[4][4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) acc[u][v] = T(0);
-    for (int64_t cb = 0; cb < n; cb += kBskTile) {
-      const int cw = (int)(n - cb < kBskTile ? n - cb : kBskTile);
-      T v[kLoads];
-#pragma unroll
-      for (int u = 0; u < kLoads; ++u) {  // all loads issued before any LDS store
-        const int e = tid + u * kBskThreads, t = e / kBskTile, j = e % kBskTile;
-        const int r = rows[t];
-        v[u] = (t < eta4 && j < cw && r >= 0) ? A[(int64_t)r * ld + cb + j] : T(0);
-      }
-      __syncthreads();  // the previous tile's reads are done
-#pragma unroll
-      for (int u = 0; u < kLoads; ++u) {
-        const int e = tid + u * kBskThreads;
-        tile[e / kBskTile][e % kBskTile] = v[u];
-      }
-      __syncthreads();
-      if (gb) {
-#pragma unroll 4
-        for (int j = 0; j < kBskTile; ++j) {
-          T a[4], c[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            a[u] = tile[4 * bi + u][j];
-            c[u] = tile[4 * bj + u][j];
-          }
-#pragma unroll
-          for (int u = 0; u < 4; ++u)
-#pragma unroll
-            for (int vv = 0; vv < 4; ++vv) acc[u][vv] += a[u] * c[vv];
-        }
-      }
-    }
-    if (gb) {
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int vv = 0; vv < 4; ++vv)
-          if (4 * bi + u < eta && 4 * bj + vv < eta) L.Gm[4 * bi + u][4 * bj + vv] = (double)acc[u][vv];
-    }
-    __syncthreads();
-    const double s2 = gram_lambda_max(L, eta);
-    if (tid == 0) {
-      if (s2 > 0.0 && isfinite(s2)) {
-        alpha_k[k] = (T)((double)eta * w / s2);
-      } else {
-        alpha_k[k] = T(0);
-        set_status(status, ST_ZERO_ROW);
-      }
-      if (norm2) norm2[k] = s2;
-    }
-    __syncthreads();  // rows, tile and L are reused by the next step
-  }
-}
-
-template <typename T>
-__global__ void fill_value(T* p, int64_t count, T v) {
-  for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
-    p[i] = v;
-}
-
-// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 
@@ -587,35 +374,6 @@ hipError_t launch_power(const LbArgs<T>& a, int64_t iters, T* v, double* est, hi
   }
   return hipGetLastError();
 }
-
-// Resident workgroups of bsk_norms (at most K).
-template <typename T>
-int bsk_grid(int64_t K) {
-  int per_cu = 0, dev = 0, cus = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)&bsk_norms<T>, kBskThreads, 0) != hipSuccess ||
-      per_cu < 1)
-    return 0;
-  if (hipGetDevice(&dev) != hipSuccess) return 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-  const int64_t g = (int64_t)per_cu * cus;
-  return (int)(K < g ? (K > 0 ? K : 1) : g);
-}
-
-template <typename T>
-hipError_t launch_bsk_norms(const BskArgs<T>& a, hipStream_t s) {
-  const int64_t ib = (a.m + 255) / 256;
-  hipLaunchKernelGGL(fill_value<T>, dim3((unsigned)(ib < 1024 ? ib : 1024)), dim3(256), 0, s, a.ones, a.m, T(1));
-  if (a.K > 0) {
-    const int G = bsk_grid<T>(a.K);
-    if (G < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(bsk_norms<T>, dim3(G), dim3(kBskThreads), 0, s, a.A, a.m, a.n, a.ld, a.tau, a.eta, a.K, a.w,
-                       a.alpha_k, a.norm2_hist, a.status);
-  }
-  return hipGetLastError();
-}
-
-template hipError_t launch_bsk_norms<float>(const BskArgs<float>&, hipStream_t);
-template hipError_t launch_bsk_norms<double>(const BskArgs<double>&, hipStream_t);
 
 template int lb_plan<float>(int64_t, int, int*, size_t*, int*, int64_t*);
 template int lb_plan<double>(int64_t, int, int*, size_t*, int*, int64_t*);
