@@ -384,12 +384,13 @@ int32_t rsk_plan_dense(const rsk_dense *A, const rsk_params *p, int32_t *out);
  * A sparse step moves a few hundred KB and is bound by latency. p->kernel
  * selects the kernel: 1 = one persistent workgroup (no cross-CU exchange),
  * 2 = the multi-workgroup kernel (one lane per nonzero, p->grid workgroups or
- * eta/8 up to the CU count, three grid barriers per step), 0 = 2 when
+ * eta/8 up to the CU count; two exchanges per step where each workgroup holds
+ * its 8 rows in one pass, else three grid barriers; same bits), 0 = 2 when
  * eta >= 4, else 1. Columns hit by several sampled rows of a step are summed
  * in int64 fixed point with a per-step power-of-two quantum (2^-41 of the
  * step's largest contribution), so x* and x are bitwise reproducible for a
  * given kernel (y_out: see rsk_params). eta <= 4096.
- * Workspace: n + 1 int64 accumulators, with y_out m int32 row counters (and
+ * Workspace: n + 1 int64 accumulators (twice with two exchanges), with y_out m int32 row counters (and
  * for the grid kernel eta coefficients), plus the grid kernel's barrier and
  * monitor words (rsk_workspace_size_csr, which depends on whether y_out is
  * set), zeroed by the call.

@@ -420,7 +420,7 @@ int32_t check_csr(const rsk_csr* A) {
 // exponent words and the monitor words.
 struct CsrPlan {
   int kernel, G;
-  size_t offYcnt, offCy, offBar, offEmax, offM, bytes;
+  size_t offYcnt, offCy, offBar, offEmax, offM, offAcc2, bytes;
 };
 
 template <typename T>
@@ -437,7 +437,7 @@ int32_t plan_csr(const rsk_csr* A, const rsk_params* p, CsrPlan* pl) {
     pl->offYcnt = o; o = align256(o + (size_t)A->m * sizeof(int));
     if (grid) { pl->offCy = o; o = align256(o + (size_t)p->eta * sizeof(T)); }
   }
-  pl->offBar = pl->offEmax = pl->offM = o;
+  pl->offBar = pl->offEmax = pl->offM = pl->offAcc2 = o;
   if (grid) {
     int G = p->grid > 0 ? p->grid : (p->eta + rpp - 1) / rpp;
     if (p->grid <= 0 && G > cus) G = cus;
@@ -445,9 +445,13 @@ int32_t plan_csr(const rsk_csr* A, const rsk_params* p, CsrPlan* pl) {
     if (G < 1 || (maxres > 0 && G > maxres)) return RSK_ERR_UNSUPPORTED;
     if ((p->eta + rpp * G - 1) / (rpp * G) > rsk::kCsrGridMaxPasses) return RSK_ERR_UNSUPPORTED;
     pl->G = G;
-    pl->offBar = o; o += 9 * 128;  // global barrier counter and 8 group counters, 128 bytes apart
+    // one pass: two exchange words a workgroup; else a global barrier counter and 8 group counters, 128
+    // bytes apart
+    const bool one = rsk::csr_one_pass(p->eta, G);
+    pl->offBar = o; o += one ? 2 * rsk::kCsrRowsMaxG * sizeof(u64) : 9 * 128;
     pl->offEmax = o; o += 64;
     pl->offM = o; o = align256(o + (size_t)G * 4 * sizeof(u64));
+    if (one) { pl->offAcc2 = o; o += align256((size_t)(A->n + 1) * sizeof(long long)); }
   }
   pl->bytes = o;
   return RSK_OK;
@@ -472,6 +476,7 @@ int32_t solve_csr_t(const rsk_csr* A, const void* b, const rsk_params* p, void* 
   a.xref = (const T*)p->x_ref; a.check_every = p->x_ref ? p->check_every : 0; a.tol = p->tol;
   a.err_hist = p->err_hist; a.status = p->status_dev;
   a.acc = (long long*)ws;
+  a.acc2 = (long long*)(w + pl.offAcc2);
   a.ycnt = p->y_out ? (int*)(w + pl.offYcnt) : nullptr;
   a.cy = p->y_out && pl.offCy ? (T*)(w + pl.offCy) : nullptr;
   a.G = pl.G;

@@ -559,12 +559,335 @@ __global__ __launch_bounds__(kGridThreads) void rska_csr_grid(CsrArgs<T> a) {
   if (g == 0 && tid == 0) a.status[1] = (int)k_done;
 }
 
+// ---------------------------------------------------------------------------
+// Multi-workgroup CSR kernel with one row of the step per 32 lanes and two exchanges a step.
+//
+// The same sums as rska_csr_grid, bit for bit, on a shorter chain of round trips:
+//  * a step's totals stay in the accumulators of its parity, and the next step's dots read x_j as
+//    S_lambda(x*_j - total_j q) on the fly; the lanes that touched a column fold its total into x*
+//    while they accumulate the next step (all dots have read it by then), so no phase of its own
+//    applies the step, and there are two exchanges a step instead of three barriers:
+//      1. after the dots: the largest exponent and any fault, one tagged word a workgroup, all of
+//         them polled by one wave of every workgroup (a barrier counter and a maximum in memory
+//         took three round trips each);
+//      2. after the fold and the accumulation: a tagged word alone.
+//  * the row pointers, b and norm of the next step's rows load while exchange 1 waits, their columns
+//    and values while exchange 2 does, the indices of the step after a step earlier.
+// Bound by latency: 1048576 x 262144, 32 nonzeros a row, eta = 512: 9.4 us a step (13.8 with three
+// barriers).
+// ---------------------------------------------------------------------------
+namespace {
+
+// 256 threads hold the rows; a fifth wave publishes and polls, so that its polls do not queue behind
+// the row waves' loads of the next step (counted in order, the first would return after all of them).
+constexpr int kRowsThreads = kGridThreads + 64;
+
+// Publish `pay` under `tag` (the workgroup's threads have passed a barrier), gather everyone's: the
+// largest payload, or -1 when the bounded wait expired. All threads get it. `pay` is the last wave's.
+__device__ __forceinline__ long long all_max(u64* slots, int g, int G, unsigned tag, unsigned pay, long long* sh) {
+  const int lane = threadIdx.x & 63;
+  if (threadIdx.x >= kGridThreads) {
+    if (lane == 0) xstore(slots + g, ((u64)tag << 32) | pay);
+    constexpr int NI = kCsrRowsMaxG / 64;
+    unsigned pending = 0, best = 0, spins = 0;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (lane + 64 * i < G) pending |= 1u << i;
+    bool late = false;
+    while (pending) {
+      u64 w[NI];
+#pragma unroll
+      for (int i = 0; i < NI; ++i) w[i] = ((pending >> i) & 1u) ? xload(slots + lane + 64 * i) : 0ull;
+#pragma unroll
+      for (int i = 0; i < NI; ++i)
+        if (((pending >> i) & 1u) && (unsigned)(w[i] >> 32) == tag) {
+          best = best > (unsigned)w[i] ? best : (unsigned)w[i];
+          pending &= ~(1u << i);
+        }
+      if (!pending) break;
+      if (++spins > kSpinLimit) { late = true; break; }
+      __builtin_amdgcn_s_sleep(1);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const unsigned o = (unsigned)__shfl_xor((int)best, off);
+      best = best > o ? best : o;
+    }
+    const bool any_late = __ballot(late) != 0;
+    if (lane == 0) *sh = any_late ? -1ll : (long long)best;
+  }
+  __syncthreads();
+  return *sh;
+}
+
+constexpr unsigned kRowsFault = 1u << 31;  // in the payload of exchange 1: a workgroup saw a fault
+
+}  // namespace
+
+template <typename T>
+__global__ __launch_bounds__(kRowsThreads) void rska_csr_rows(CsrArgs<T> a) {
+  constexpr int RPP = kCsrGridRowsPerPass;
+  constexpr int NW = kRowsThreads / 64;
+  __shared__ double wmax[NW];
+  __shared__ int werr[NW];
+  __shared__ long long sh[2];  // the results of the two exchanges
+  __shared__ double mon[2 * NW + 2];
+  const int g = blockIdx.x, G = a.G, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int p = tid & 31;
+  const int eta = a.eta;
+  const int t = g * RPP + (tid >> 5);  // this half wave's slot of every step
+  const bool rows = tid < kGridThreads;    // uniform over a wave
+  const bool live = rows && t < eta;
+  u64 *slot1 = a.bar, *slot2 = a.bar + kCsrRowsMaxG;
+  int stop_code = 0;
+
+  // x*_0 over this workgroup's column block
+  const int64_t j0 = (int64_t)g * a.n / G, j1 = (int64_t)(g + 1) * a.n / G;
+  if (!a.warm)
+    for (int64_t j = j0 + tid; j < j1; j += kRowsThreads) st_ag(a.x_star + j, T(0));
+
+  // the row of the step: index (-1: out of range or no row), entries [r0, r1), b, norm over weight, and
+  // the lane's first entry (column -1: none)
+  int i = -1, j = -1;
+  int64_t r0 = 0, r1 = 0;
+  T bi = T(0), rn = T(1), v = T(0);
+  auto row_of = [&](int raw) { return live && raw >= 0 && (int64_t)raw < a.m ? raw : -1; };
+  // (every address valid, no branch: a load inside one is waited for at once)
+  auto fetch_row = [&](int row, int64_t& q0, int64_t& q1, T& b, T& nrm) {
+    const int ii = row < 0 ? 0 : row;
+    q0 = a.row_ptr[ii];
+    q1 = a.row_ptr[ii + 1];
+    b = a.b[ii];
+    nrm = weighted_rn(a.r2, a.row_w, ii);
+  };
+  auto fetch_entry = [&](int row, int64_t q0, int64_t q1, int& jj, T& vv) {
+    const bool on = row >= 0 && q0 + p < q1;
+    const int32_t* pc = on ? a.col + (q0 + p) : a.idx;
+    const T* pv = on ? a.val + (q0 + p) : a.b;
+    jj = *pc;
+    vv = *pv;
+    return on;
+  };
+  bool on = false;
+  int raw1 = -1;  // the next step's index as read
+  if (a.K > 0) {
+    i = row_of(live ? a.idx[t] : -1);
+    fetch_row(i, r0, r1, bi, rn);
+    on = fetch_entry(i, r0, r1, j, v);
+    if (live && a.K > 1) raw1 = a.idx[(int64_t)eta + t];
+  }
+  // the step before's columns, to be folded
+  bool pon = false;
+  int pj = 0, pe = 0;
+  int64_t pr0 = 0, pr1 = 0;
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  if (all_max(slot2, g, G, 1u, 0u, &sh[1]) < 0) stop_code = ST_ABORTED;
+
+  int64_t k_done = 0;
+  for (int64_t k = 0; k < a.K && !stop_code; ++k) {
+    const T ak = a.alpha_k ? a.alpha_k[k] : a.alpha;
+    const unsigned tag = (unsigned)(k + 1);
+    long long* accc = (k & 1) ? a.acc2 : a.acc;   // this step's totals
+    long long* accp = (k & 1) ? a.acc : a.acc2;   // the step before's, pending
+    int lerr = live && i < 0 ? ST_INDEX : 0;
+    auto x_at = [&](int col) {
+      const T z = ld_ag(a.x_star + col);
+      const long long tot = ld_ag(accp + col);
+      return shrink(tot != 0 ? (T)((double)z - ldexp((double)tot, pe - 40)) : z, a.lambda);
+    };
+
+    // the dot, c_t and the largest contribution; x* of the column to be folded (nobody writes x* before
+    // exchange 1, so it is the value the fold needs)
+    T dot = T(0);
+    T pz = T(0);
+    if (rows) pz = ld_ag(a.x_star + (pon ? pj : 0));
+    if (on && (j < 0 || (int64_t)j >= a.n)) { lerr = ST_INDEX; on = false; }
+    if (on) dot = v * x_at(j);
+    if (live && i >= 0)
+      for (int64_t q = r0 + p + 32; q < r1; q += 32) {
+        const int jq = a.col[q];
+        const T vq = a.val[q];
+        if (jq < 0 || (int64_t)jq >= a.n) { lerr = ST_INDEX; continue; }
+        dot += vq * x_at(jq);
+      }
+    dot = sum32(dot);
+    T c = T(0);
+    double vmax = 0.0;
+    if (live && i >= 0) {
+      if (rn == T(0)) { if (!lerr) lerr = ST_ZERO_ROW; c = T(NAN); }
+      else c = (ak / T(eta)) * (dot - bi) / rn;
+      if (!isfinite(c) && !lerr) lerr = ST_NONFINITE;
+      if (on) vmax = fabs((double)(c * v));
+      for (int64_t q = r0 + p + 32; q < r1; q += 32) vmax = fmax(vmax, fabs((double)(c * a.val[q])));
+    }
+    int yown = 0;
+    if (a.y && live && i >= 0 && p == 0) {
+      st_ag(a.cy + t, c);
+      yown = __hip_atomic_fetch_add(a.ycnt + i, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0;
+    }
+    if (lerr) set_status(a.status, lerr);
+    for (int off = 32; off > 0; off >>= 1) vmax = fmax(vmax, __shfl_xor(vmax, off));
+    const bool werror = __ballot(lerr != 0) != 0;
+    if (lane == 0) { wmax[wave] = vmax; werr[wave] = werror; }
+    if (a.y) __builtin_amdgcn_s_waitcnt(0);  // the coefficients and counts are complete
+    __syncthreads();
+    unsigned pay = 0;
+    if (!rows) {
+      double m = 0.0;
+      int bad = 0;
+      for (int w = 0; w < NW; ++w) { m = fmax(m, wmax[w]); bad |= werr[w]; }
+      if (m > 0.0 && isfinite(m)) pay = (unsigned)(ilogb(m) + kEBias);
+      if (bad) pay |= kRowsFault;
+    }
+    // the next step's rows, and the indices of the step after
+    const bool has_next = k + 1 < a.K;
+    const int ni = has_next ? row_of(raw1) : -1;
+    int64_t nr0 = 0, nr1 = 0;
+    T nb = T(0), nrn = T(1);
+    if (rows) {
+      fetch_row(ni, nr0, nr1, nb, nrn);
+      raw1 = a.idx[(k + 2 < a.K ? k + 2 : a.K - 1) * (int64_t)eta + (live ? t : 0)];
+    }
+    const long long m1 = all_max(slot1, g, G, tag, pay, &sh[0]);
+    if (m1 < 0) { stop_code = ST_ABORTED; break; }
+    if ((unsigned)m1 & kRowsFault) { stop_code = -1; break; }  // recorded by the workgroup that saw it
+
+    // dual output, as in rska_csr_grid
+    if (a.y && live && __shfl(yown, lane & 32)) {
+      int cnt = 0;
+      if (p == 0) cnt = __hip_atomic_exchange(a.ycnt + i, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      cnt = __shfl(cnt, lane & 32);
+      T sc = T(0);
+      if (cnt == 1) {
+        if (p == 0) sc = c;
+      } else {
+        const int32_t* tk = a.idx + k * (int64_t)eta;
+        for (int u = p; u < eta; u += 32)
+          if (tk[u] == i) sc += ld_ag(a.cy + u);
+      }
+      sc = sum32(sc);
+      if (p == 0) st_ag(a.y + i, ld_ag(a.y + i) - sc);
+    }
+
+    // the next step's first entries; fold the step before into x*; accumulate this step
+    int nj = -1;
+    T nv = T(0);
+    bool non = false;
+    if (rows) non = fetch_entry(ni, nr0, nr1, nj, nv);
+    // (by the lane that swaps the column's total out)
+    auto take = [&](int col) {
+      return __hip_atomic_exchange(accp + col, 0ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    auto fold = [&](int col, T z, long long tot) {
+      if (tot != 0)
+        __hip_atomic_store(a.x_star + col, (T)((double)z - ldexp((double)tot, pe - 40)), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    };
+    long long ptot = 0;
+    if (pon) ptot = take(pj);
+    const int e = (int)m1 - kEBias;
+    auto add = [&](int col, T val) {
+      const long long w = (long long)llrint(ldexp((double)(c * val), 40 - e));
+      __hip_atomic_fetch_add(accc + col, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
+    if (m1 > 0) {
+      if (on) add(j, v);
+      if (live)
+        for (int64_t q = r0 + p + 32; q < r1; q += 32) add(a.col[q], a.val[q]);
+    }
+    fold(pj, pz, ptot);
+    for (int64_t q = pr0 + p + 32; q < pr1; q += 32) {
+      const int col = a.col[q];
+      const long long tot = take(col);
+      if (tot != 0) fold(col, ld_ag(a.x_star + col), tot);
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // this thread's atomics and stores are complete
+    __syncthreads();
+    if (all_max(slot2, g, G, tag + 1, 0u, &sh[1]) < 0) { stop_code = ST_ABORTED; break; }
+    k_done = k + 1;
+    pon = on;
+    pj = j;
+    pe = e;
+    pr0 = r0;
+    pr1 = live ? r1 : r0;
+    i = ni;
+    r0 = nr0;
+    r1 = nr1;
+    bi = nb;
+    rn = nrn;
+    on = non;
+    j = nj;
+    v = nv;
+
+    if (a.xref && a.check_every > 0 && (k + 1) % a.check_every == 0) {
+      const unsigned mtag = (unsigned)((k + 1) / a.check_every);
+      double e2 = 0.0, r2s = 0.0;
+      for (int64_t c2 = j0 + tid; c2 < j1; c2 += kRowsThreads) {
+        const T z = ld_ag(a.x_star + c2);
+        const long long tot = ld_ag(accc + c2);
+        const double rf = (double)a.xref[c2];
+        const double d =
+            (double)shrink(tot != 0 ? (T)((double)z - ldexp((double)tot, e - 40)) : z, a.lambda) - rf;
+        e2 += d * d;
+        r2s += rf * rf;
+      }
+      e2 = wave_sum(e2);
+      r2s = wave_sum(r2s);
+      if (lane == 0) { mon[2 * wave] = e2; mon[2 * wave + 1] = r2s; }
+      __syncthreads();
+      if (tid == 0) {
+        double se = 0.0, sr = 0.0;
+        for (int w = 0; w < NW; ++w) { se += mon[2 * w]; sr += mon[2 * w + 1]; }
+        put_tagged(&a.xM[(size_t)g * 4], se, mtag);
+        put_tagged(&a.xM[(size_t)g * 4 + 2], sr, mtag);
+      }
+      __syncthreads();
+      int merr = 0;
+      if (wave == 0) {
+        double se = 0.0, sr = 0.0;
+        for (int q = lane; q < G; q += 64) {
+          se += wait_tagged<double>(&a.xM[(size_t)q * 4], mtag, merr);
+          sr += wait_tagged<double>(&a.xM[(size_t)q * 4 + 2], mtag, merr);
+        }
+        se = wave_sum(se);
+        sr = wave_sum(sr);
+        if (lane == 0) {
+          const double err = sr > 0.0 ? sqrt(se / sr) : sqrt(se);
+          if (g == 0 && a.err_hist) a.err_hist[mtag - 1] = err;
+          mon[2 * NW] = err;
+        }
+      }
+      if (merr) set_status(a.status, merr);
+      if (__syncthreads_or(merr)) { stop_code = ST_ABORTED; break; }
+      if (a.tol > 0.0 && mon[2 * NW] <= a.tol) break;
+    }
+  }
+  // x*_K and x_K: the totals of the last completed step are still pending. Nothing writes x* or the
+  // accumulators any more: every workgroup has passed that step's second exchange (and, after a
+  // fault, the first one of the step that saw it).
+  const long long* accl = (k_done & 1) ? a.acc : a.acc2;
+  for (int64_t c2 = j0 + tid; c2 < j1; c2 += kRowsThreads) {
+    T z = ld_ag(a.x_star + c2);
+    const long long tot = k_done > 0 ? ld_ag(accl + c2) : 0ll;
+    if (tot != 0) z = (T)((double)z - ldexp((double)tot, pe - 40));
+    a.x_star[c2] = z;
+    a.x[c2] = shrink(z, a.lambda);
+  }
+  if (stop_code > 0 && tid == 0) set_status(a.status, stop_code);
+  if (g == 0 && tid == 0) a.status[1] = (int)k_done;
+}
+
 template <typename T>
 int csr_grid_max_resident() {
   int per_cu = 0;
+  int one = 0;  // of either kernel
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)&rska_csr_grid<T>, kGridThreads, 0) !=
-      hipSuccess)
+          hipSuccess ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&one, (const void*)&rska_csr_rows<T>, kRowsThreads, 0) !=
+          hipSuccess)
     return 0;
+  if (one < 1) return 0;  // (its grids are at most one workgroup a CU)
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
@@ -575,6 +898,8 @@ template <typename T>
 hipError_t launch_csr_grid(CsrArgs<T>& a, hipStream_t stream) {
   if (a.G < 1 || a.G > csr_grid_max_resident<T>()) return hipErrorCooperativeLaunchTooLarge;
   void* args[] = {&a};
+  if (csr_one_pass(a.eta, a.G))
+    return launch_persistent((const void*)&rska_csr_rows<T>, dim3(a.G), dim3(kRowsThreads), args, 0, stream);
   return launch_persistent((const void*)&rska_csr_grid<T>, dim3(a.G), dim3(kGridThreads), args, 0, stream);
 }
 

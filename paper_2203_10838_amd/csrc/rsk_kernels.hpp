@@ -134,21 +134,26 @@ struct CsrArgs {
   double tol;
   double* err_hist;
   int* status;
-  long long* acc;         // n + 1 int64 accumulators (the last a spare), zero on entry and on exit
+  long long* acc;         // n + 1 int64 accumulators (the last a spare), zero on entry
+  long long* acc2;        // one-pass grid kernel: n + 1 more, for the steps of odd number
   int* ycnt;              // [m] slots of the current step per row (y only; zero on entry and between steps)
   T* cy;                  // [eta] the step's coefficients by slot (grid kernel, y only)
   // grid kernel only
   int G;                  // workgroups
-  u64* bar;               // grid barrier counter (zero on entry)
+  u64* bar;               // grid barrier counter, or 2 * kCsrRowsMaxG exchange words (zero on entry)
   int* emax;              // [2] biased max exponent of a step's contributions (zero on entry)
   u64* xM;                // monitor words [G][4]
 };
 
 template <typename T>
 hipError_t launch_csr(CsrArgs<T>& a, hipStream_t stream);
-// Multi-workgroup CSR kernel (one lane per nonzero, three grid barriers per step).
+// Multi-workgroup CSR kernels (one lane per nonzero): where every workgroup holds its 8 rows of a
+// step in one pass and G <= kCsrRowsMaxG, the one with two exchanges a step (rska_csr_rows), else
+// the one with three grid barriers (rska_csr_grid).
+constexpr int kCsrRowsMaxG = 256;
 constexpr int kCsrGridRowsPerPass = 8;   // rows per workgroup and pass (256 threads, 32 lanes a row)
 constexpr int kCsrGridMaxPasses = 8;
+inline bool csr_one_pass(int eta, int G) { return G <= kCsrRowsMaxG && eta <= kCsrGridRowsPerPass * G; }
 template <typename T>
 int csr_grid_max_resident();
 template <typename T>
