@@ -489,11 +489,13 @@ int32_t solve_csr_t(const rsk_csr* A, const void* b, const rsk_params* p, void* 
   return e == hipSuccess ? RSK_OK : RSK_ERR_HIP;
 }
 
+constexpr int64_t kWideWork = 3900000;
 struct MultiPlan {
   int S, eta_pad, S2;
   int64_t kspan;
   int kernel;       // 1: step kernels (four per step), 2: one persistent launch for all K steps,
                     // 3: the step kernels with wide product tiles (128 x 128, or 128 x 64 for R <= 64)
+  int tn;           // R edge of a product tile (64 or 128)
   int tile;         // 64 (kernels 1, 2) or 128 (kernel 3): the tile edge of the products
   int pS;           // persistent launch: its split of the n columns (kspan rounded up to 64)
   int64_t pkspan;
@@ -511,12 +513,20 @@ int32_t plan_multirhs(const rsk_dense* A, int32_t R, const rsk_params* p, MultiP
   rsk_tune_entry te;
   const bool tuned = tune_find(RSK_TUNE_MULTIRHS, A->dtype, A->m, A->n, p->eta, R, &te);
   // the kernel: p->kernel 1, 2 or 3 as asked, else a tuned choice, else the wide-tile step kernels
-  // when R and eta each fill at least one 128 tile, the 64 x 64 ones below that
+  // when eta fills at least one 128 tile and R does, or the step's rows are long and many enough that
+  // reading them (kWideWork elements) is what takes the time; else the 64 x 64 ones. Measured, us a
+  // step, 64 x 64 / wide (n, eta, R): 1000, 128, 96 22.9 / 21.2; 2048, 205, 256 26.9 / 27.5; 4096, 410,
+  // 256 43.1 / 35.4; 8192, 820, 256 104 / 69; 32768, 820, 256 375 / 214; with R = 64: 4096, 410 26.8 / 26.8;
+  // 6000, 601 32.2 / 32.5; 20000, 200 48.9 / 37.5; 8192, 820 44.0 / 37.1
   pl->kernel = p->kernel >= 1 ? p->kernel
-             : (tuned && te.v2 >= 1 && te.v2 <= 3 ? (int)te.v2 : (R > 64 && p->eta >= 128 ? 3 : 1));
+             : (tuned && te.v2 >= 1 && te.v2 <= 3 ? (int)te.v2 : (p->eta >= 128 && (R > 64 || p->eta * A->n >= kWideWork) ? 3 : 1));
   pl->tile = pl->kernel == 3 ? 128 : 64;
-  const int tn = pl->tile == 128 && R <= 64 ? 64 : pl->tile;  // the R edge of a product tile
   pl->eta_pad = (p->eta + pl->tile - 1) / pl->tile * pl->tile;
+  // the R edge of a product tile: wide tiles of 128 where they fill the device in splits of at least 256
+  // columns, else 64 (2048, 205, 256 27.5 us a step with 64, 29.4 with 128 and the device half empty)
+  const int64_t most_s = (A->n + 255) / 256;
+  const int tn = pl->tile == 128 && (R <= 64 || pl->eta_pad / 128 * ((R + 127) / 128) * most_s < cus) ? 64 : pl->tile;
+  pl->tn = tn;
   const int tiles = (pl->eta_pad / pl->tile) * ((R + tn - 1) / tn);
   // about three 256-thread workgroups per CU for the n-long products, in whole XCD rounds (the
   // tiles of a split share one L2); or one 512-thread wide-tile workgroup per CU, rounded down (a
@@ -524,8 +534,9 @@ int32_t plan_multirhs(const rsk_dense* A, int32_t R, const rsk_params* p, MultiP
   int S = pl->tile == 128 ? cus / tiles : (3 * cus + tiles - 1) / tiles;
   if (S >= 8 && pl->tile != 128) S = (S + 7) / 8 * 8;
   if (tuned && te.v0 >= 1) S = (int)(te.v0 < 4096 ? te.v0 : 4096);
-  // at least 256 columns a split by the built-in rule, at least 64 (one stage) for a tuned split
-  const int64_t max_s = tuned && te.v0 >= 1 ? (A->n + 63) / 64 : (A->n + 255) / 256;
+  // at least 256 columns a split by the built-in rule (128, four stages, for the wide tiles: 4096, 410,
+  // R = 128 31.5 us a step with 256, 29.6 with 128), at least 64 for a tuned split
+  const int64_t max_s = tuned && te.v0 >= 1 ? (A->n + 63) / 64 : pl->tile == 128 ? (A->n + 127) / 128 : most_s;
   if (S > max_s) S = (int)max_s;
   if (S < 1) S = 1;
   pl->kspan = (A->n + S - 1) / S;
@@ -651,7 +662,7 @@ void fill_multirhs(const rsk_dense* A, const void* B, int32_t R, const rsk_param
   a.x_star = (float*)X_star; a.x = (float*)X; a.warm = p->warm_start ? 1 : 0;
   a.status = p->status_dev;
   a.Y = (float*)(w + pl.offY); a.C = (float*)(w + pl.offC);
-  a.S = pl.S; a.eta_pad = pl.eta_pad; a.kspan = pl.kspan; a.tile = pl.tile;
+  a.S = pl.S; a.eta_pad = pl.eta_pad; a.kspan = pl.kspan; a.tile = pl.tile; a.tn = pl.tn;
   // the row-split epilogue moves float4 of X* and X: used only when both are 16-byte aligned
   const bool al = ((uintptr_t)X_star) % 16 == 0 && ((uintptr_t)X) % 16 == 0;
   a.S2 = (pl.S2 > 1 && al) ? pl.S2 : 1;

@@ -476,143 +476,257 @@ __global__ void init_multirhs(float* Xs, float* X, size_t total, float lambda, i
 }
 
 // ---------------------------------------------------------------------------
-// Wide-tile products (the plan's tile = 128): TM x TN outputs per 256-thread workgroup
-// (TM = 128; TN = 128, or 64 for R <= 64), four waves of (TM/2) x (TN/2), each a grid of
-// (TM/32) x (TN/32) v_mfma_f32_16x16x4f32 blocks. K advances 32 per stage. A tile of twice the
-// width reads half the bytes per product of the 64 x 64 tiles: those are bound by the rate at
-// which a CU pulls its operands through L2 (the same step time whether the sampled rows spread
-// over the whole matrix or fit in L2), not by HBM or by the matrix cores.
-// Loads are branch-free (every address valid; positions outside the product are zeroed when
-// the stage is stored to LDS), and each stage's loads are issued before the previous stage's
-// products.
+// Wide-tile products (the plan's tile = 128): TM x TN outputs per 512-thread workgroup (TM = 128;
+// TN = 128, or 64), eight waves in a 4 x 2 grid, two a SIMD, so that one wave's products cover the
+// other's LDS reads and splitting.
+//
+// float32 operands on the bfloat16 matrix cores. Each operand element is split exactly into three
+// bfloat16 pieces, a = a1 + a2 + a3 (8 bits each: a1 truncates a, so it never overflows; a2 rounds
+// a - a1; a3 is what is left), and a product is the six terms a1 b3, a2 b2, a3 b1, a1 b2, a2 b1, a1 b1,
+// each an exact product added in float32. The three terms left out are below 2^-24 of the product
+// together, one rounding of the float32 matrix cores' own chain, which makes one a term where these
+// make one a stage (a1 b1 has accumulators of its own): the sums are closer to the exact ones (20 steps
+// of 32768 x 8192, R = 256, eta = 820: x* off by 1.3e-7 of its norm, 3.0e-7 on the float32 cores; n = 1280
+// ... 7000, R = 68 ... 256: 0.5 to 0.8 of the float32 cores' error). Six bfloat16 products take 3/8 of the
+// time of one in float32. Per launch at that size: A_tau X 33 us (44 in float32), the fused update 36 (44).
+//
+// K advances 32 a stage. A thread loads 8 consecutive k of two columns (8 float2 loads, a wave one row's
+// 512 bytes; where k runs along memory, of two rows: 4 float4), splits them and writes the pieces as
+// 16-byte words, octet-major: LDS word (piece, octet of k, position). A fragment of
+// v_mfma_f32_16x16x32_bf16 (row l % 16, octet l / 16) is then one conflict-free 16-byte read. Four
+// waves load one operand and four the other. Loads of one word a lane cost as many cycles of the
+// address unit as wide ones and bounded the products (51 us an A^T product, 31 without its loads).
+// Two register buffers of raw loads and two LDS buffers: stage s + 1 is split and stored while stage
+// s's products run (one barrier a stage), with the loads of the stage after in flight.
 // ---------------------------------------------------------------------------
 namespace {
 
 constexpr int SKW = 32;  // K per stage of the wide-tile products
-// The wide-tile products run 512 threads: 8 waves in a 4 x 2 grid over the tile, two a SIMD, so
-// that one wave's MFMAs cover the other's LDS reads and barriers (with one wave a SIMD they are
-// exposed: these grids put about one workgroup on each CU).
 constexpr int NTW = 512, WGM = 4, WGN = 2;
+constexpr int OCT = SKW / 8;  // octets of k a stage
 
-template <int TN>
-struct WideMap {  // a row of TN floats: TN/4 float4 across consecutive threads
-  static constexpr int cpr = TN / 4;           // float4 per row
-  static constexpr int rpp = NTW / cpr;        // rows per pass
-  static constexpr int passes = SKW / rpp;     // passes over the SKW rows of a stage
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef unsigned u4v __attribute__((ext_vector_type(4)));
+
+// LDS words (16 bytes) of one buffer of an operand tile of T rows or columns: 3 pieces x OCT octets, the
+// octets 64 bytes off a multiple of the banks so that writes of four octets side by side do not collide
+template <int T>
+struct SplitTile {
+  static constexpr int pitch = T + 4, words = 3 * OCT * pitch;
+  static __device__ __forceinline__ int at(int piece, int oct, int i) { return (piece * OCT + oct) * pitch + i; }
 };
 
+// Tile position of column x (of a pair loaded together: columns 2c, 2c + 1 go to blocks of 16 positions
+// side by side, so that a store's lanes write consecutive words) and the column at position p.
+__device__ __forceinline__ int tile_pos(int x) { return (x / 32) * 32 + (x % 2) * 16 + (x / 2) % 16; }
+__device__ __forceinline__ int tile_col(int p) { return 2 * ((p / 32) * 16 + p % 16) + (p / 16) % 2; }
+
+__device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+  const f2 v = {lo, hi};
+  return __builtin_bit_cast(unsigned, __builtin_convertvector(v, b2));
+}
+
+// the three pieces of eight values, packed
+__device__ __forceinline__ void split8(const float (&f)[8], u4v (&w)[3]) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const unsigned u0 = __float_as_uint(f[2 * q]), u1 = __float_as_uint(f[2 * q + 1]);
+    w[0][q] = __builtin_amdgcn_perm(u1, u0, 0x07060302);  // the upper halves
+    const float r0 = f[2 * q] - __uint_as_float(u0 & 0xffff0000u);
+    const float r1 = f[2 * q + 1] - __uint_as_float(u1 & 0xffff0000u);
+    const unsigned m = pack_bf16(r0, r1);
+    w[1][q] = m;
+    w[2][q] = pack_bf16(r0 - __uint_as_float(m << 16), r1 - __uint_as_float(m & 0xffff0000u));
+  }
+}
+
+template <int T>
+__device__ __forceinline__ void put8(u4v* tile, int oct, int i, const float (&f)[8]) {
+  u4v w[3];
+  split8(f, w);
+#pragma unroll
+  for (int c = 0; c < 3; ++c) tile[SplitTile<T>::at(c, oct, i)] = w[c];
+}
+// eight rows of a column pair
+struct Pairs {
+  float2 f[8];
+};
+template <int T>
+__device__ __forceinline__ void put_pairs(u4v* tile, int oct, int col, const Pairs& u) {
+  const float f0[8] = {u.f[0].x, u.f[1].x, u.f[2].x, u.f[3].x, u.f[4].x, u.f[5].x, u.f[6].x, u.f[7].x};
+  const float f1[8] = {u.f[0].y, u.f[1].y, u.f[2].y, u.f[3].y, u.f[4].y, u.f[5].y, u.f[6].y, u.f[7].y};
+  put8<T>(tile, oct, tile_pos(col), f0);
+  put8<T>(tile, oct, tile_pos(col + 1), f1);
+}
+// A wave's 16 x 16 blocks: a1 b1 in hi, the other terms in lo (2^-8 of it, so that their roundings do not
+// count)
 template <int TM, int TN>
-__device__ __forceinline__ void mma_stage_w(const float* As, int a_rows, const float* Bs, int wm, int wn,
-                                            int lane, f4 (&acc)[TM / (16 * WGM)][TN / (16 * WGN)]) {
-  // a_rows: As is row-major [TM][SKW + 4] (true) or k-major [SKW][TM + 16] (false)
-  constexpr int BI = TM / (16 * WGM), BJ = TN / (16 * WGN), PB = TN + 16, PA = TM + 16, LDR = SKW + 4;
+struct WideAcc {
+  f4 hi[TM / (16 * WGM)][TN / (16 * WGN)], lo[TM / (16 * WGM)][TN / (16 * WGN)];
+  __device__ __forceinline__ void zero() {
+#pragma unroll
+    for (int i = 0; i < TM / (16 * WGM); ++i)
+#pragma unroll
+      for (int j = 0; j < TN / (16 * WGN); ++j) hi[i][j] = lo[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+  }
+  __device__ __forceinline__ float sum(int i, int j, int v) const { return hi[i][j][v] + lo[i][j][v]; }
+};
+template <int TM, int TN>
+__device__ __forceinline__ void mma_stage_w(const u4v* As, const u4v* Bs, int wm, int wn, int lane,
+                                            WideAcc<TM, TN>& acc) {
+  constexpr int BI = TM / (16 * WGM), BJ = TN / (16 * WGN);
   const int li = lane & 15, lk = lane >> 4;
+  bf8 a[3][BI], b[3][BJ];
 #pragma unroll
-  for (int k0 = 0; k0 < SKW; k0 += 4) {
-    float a[BI], b[BJ];
+  for (int c = 0; c < 3; ++c) {
 #pragma unroll
-    for (int i = 0; i < BI; ++i) {
-      const int m = wm * (TM / WGM) + i * 16 + li;
-      a[i] = a_rows ? As[m * LDR + k0 + lk] : As[(k0 + lk) * PA + m];
-    }
+    for (int i = 0; i < BI; ++i)
+      a[c][i] = __builtin_bit_cast(bf8, As[SplitTile<TM>::at(c, lk, wm * (TM / WGM) + i * 16 + li)]);
 #pragma unroll
-    for (int j = 0; j < BJ; ++j) b[j] = Bs[(k0 + lk) * PB + wn * (TN / WGN) + j * 16 + li];
+    for (int j = 0; j < BJ; ++j)
+      b[c][j] = __builtin_bit_cast(bf8, Bs[SplitTile<TN>::at(c, lk, wn * (TN / WGN) + j * 16 + li)]);
+  }
+  constexpr int ta[6] = {0, 1, 2, 0, 1, 0}, tb[6] = {2, 1, 0, 1, 0, 0};
+#pragma unroll
+  for (int q = 0; q < 6; ++q)
 #pragma unroll
     for (int i = 0; i < BI; ++i)
 #pragma unroll
-      for (int j = 0; j < BJ; ++j) acc[i][j] = mfma16(a[i], b[j], acc[i][j]);
+      for (int j = 0; j < BJ; ++j) {
+        f4& d = q < 5 ? acc.lo[i][j] : acc.hi[i][j];
+        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ta[q]][i], b[tb[q]][j], d, 0, 0, 0);
+      }
+}
+
+// Two words at a wave-uniform address plus a byte offset a lane keeps for the whole product, as a
+// buffer load: the address arithmetic is scalar, and offsets from `bytes` on read as zero, so that the
+// ends of a product need no masks.
+typedef unsigned u2v __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float2 load_at(const float* base, unsigned lane_bytes, int bytes) {
+  const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base), 0, bytes, 0x00020000);
+  const u2v v = __builtin_bit_cast(u2v, __builtin_amdgcn_raw_buffer_load_b64(r, lane_bytes, 0, 0));
+  return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
+}
+// q < left ? -1 (no bound) : 0, in a scalar register (the compiler's own select ends in a vector
+// register, and with it a loop around each load)
+__device__ __forceinline__ int unbounded_if(int q, int left) {
+  int v;
+  asm("s_cmp_lt_i32 %1, %2\n\ts_cselect_b32 %0, -1, 0" : "=s"(v) : "s"(q), "s"(left) : "scc");
+  return v;
+}
+
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
+// The waves' share of a k-major operand with consecutive rows (row k at p + k * R): TN / 2 column pairs x
+// OCT octets over 4 (TN = 128) or 2 (TN = 64) waves, a wave one octet or two.
+template <int TN>
+struct RowPairs {
+  int wv, oct, col;   // wave of the share, the lane's octet and column
+  unsigned off;       // the lane's byte offset from row 8 * o0
+  bool has;
+  int o0;
+  __device__ __forceinline__ RowPairs(int w, int lane, int r0, int R) {
+    constexpr int PL = TN / 2;  // pairs a row
+    wv = w;
+    has = wv >= 0 && wv < OCT * PL / 64;
+    o0 = wv * (64 / PL);
+    oct = o0 + lane / PL;
+    col = lane % PL * 2;
+    off = 4u * (unsigned)(lane / PL * 8 * R + (r0 + col < R ? col : 0));
+  }
+  // rows k + 8 * o0 ... of p (the tile's first column), zeros from row `end` on
+  __device__ __forceinline__ void load(const float* p, int R, int64_t k, int64_t end, Pairs& u) const {
+    constexpr int kRows = 8 + 8 * (64 / (TN / 2) - 1);  // rows a load may reach past its first
+    const int left = uniform((int)(end - k - 8 * o0 > 64 ? 64 : end - k - 8 * o0));
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      int rows = left - q;  // scalar clamp to 0 ... kRows
+      asm("s_max_i32 %0, %0, 0\n\ts_min_i32 %0, %0, %1" : "+s"(rows) : "i"(kRows) : "scc");
+      u.f[q] = load_at(p + (k + 8 * o0 + q) * (int64_t)R, off, rows * R * 4);
+    }
+  }
+};
+
+// The stages of a product: load(stage, buffer) issues a stage's loads, put(buffer, LDS buffer) splits and
+// stores them. Stage j's loads go to register buffer j % 2, unconditionally and past the end too (they
+// read as zeros there): where a load may have been skipped, the compiler makes every later wait one
+// for all loads.
+template <int TM, int TN, typename Buf, typename Load, typename Put>
+__device__ __forceinline__ void stages_w(int nst, const u4v* As, const u4v* Bs, int wm, int wn, int lane,
+                                         WideAcc<TM, TN>& acc, Load load, Put put) {
+  if (nst <= 0) return;
+  constexpr int ASZ = SplitTile<TM>::words, BSZ = SplitTile<TN>::words;
+  Buf b0, b1;
+  load(0, b0);
+  load(1, b1);
+  put(b0, 0);
+  load(2, b0);
+  __syncthreads();
+  for (int st = 0; st < nst; st += 2) {
+    mma_stage_w<TM, TN>(As, Bs, wm, wn, lane, acc);
+    put(b1, 1);
+    load(st + 3, b1);
+    __syncthreads();
+    // (an odd count ends with a stage of zeros)
+    mma_stage_w<TM, TN>(As + ASZ, Bs + BSZ, wm, wn, lane, acc);
+    put(b0, 0);
+    load(st + 4, b0);
+    __syncthreads();
   }
 }
 
-// acc = A_tau^T C over the sampled rows t < eta (taus in LDS) for output columns j0.. (TM) and
-// right-hand sides r0.. (TN): the A operand is k-major in memory (row tau_t, columns j), as is C.
+// The stages with each wave's part of the loading: A (a_role), the other operand (has) or none. Each
+// part is a loop of its own (the same barriers), so that its loads stand in no branch.
+template <int TM, int TN, typename Buf, typename LA, typename PA, typename LB, typename PB>
+__device__ __forceinline__ void roles_w(bool a_role, bool has, int nst, const u4v* As, const u4v* Bs, int wm, int wn,
+                                        int lane, WideAcc<TM, TN>& acc, LA load_a, PA put_a,
+                                        LB load_b, PB put_b) {
+  if (a_role)
+    stages_w<TM, TN, Buf>(nst, As, Bs, wm, wn, lane, acc, load_a, put_a);
+  else if (has)
+    stages_w<TM, TN, Buf>(nst, As, Bs, wm, wn, lane, acc, load_b, put_b);
+  else
+    stages_w<TM, TN, Buf>(nst, As, Bs, wm, wn, lane, acc, [](int, Buf&) {}, [](Buf&, int) {});
+}
+
+// acc = A_tau^T C over the sampled rows t < eta (taus in LDS, padded with a valid row to whole stages)
+// for output columns j0.. (TM) and right-hand sides r0.. (TN): both operands k-major in memory (row
+// tau_t, columns j; row t, columns r).
 template <int TM, int TN>
 __device__ __forceinline__ void att_mainloop_w(const float* __restrict__ A, int64_t ld, int64_t n,
                                                const int* taus, int eta, const float* __restrict__ C, int R,
-                                               int64_t j0, int r0, float* As, float* Bs,
-                                               f4 (&acc)[TM / (16 * WGM)][TN / (16 * WGN)]) {
-  using MA = WideMap<TM>;
-  using MB = WideMap<TN>;
-  constexpr int PA = TM + 16, PB = TN + 16;
-  static_assert(MA::passes >= 1 && MB::passes >= 1 && MA::passes * MA::rpp == SKW && MB::passes * MB::rpp == SKW,
-                "a stage's rows split into whole passes");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int ar = tid / MA::cpr, ac = (tid % MA::cpr) * 4;
-  const int br = tid / MB::cpr, bc = (tid % MB::cpr) * 4;
-  const bool colok = j0 + ac < n, rok = r0 + bc < R;
-  const int64_t jc = colok ? j0 + ac : 0;
-  const int rc = rok ? r0 + bc : 0;
-  struct Buf {
-    float4 a[MA::passes], b[MB::passes];
-    bool ka[MA::passes], kb[MB::passes];
-  };
-  auto load = [&](int tb, Buf& st) {
-    int rows[MA::passes];
-#pragma unroll
-    for (int i = 0; i < MA::passes; ++i) {
-      const int t = tb + ar + MA::rpp * i;
-      rows[i] = taus[t < eta ? t : 0];
-    }
-#pragma unroll
-    for (int i = 0; i < MA::passes; ++i) {
-      const int t = tb + ar + MA::rpp * i;
-      st.a[i] = *reinterpret_cast<const float4*>(A + (int64_t)rows[i] * ld + jc);
-      st.ka[i] = t < eta && colok;
-    }
-#pragma unroll
-    for (int i = 0; i < MB::passes; ++i) {
-      const int t = tb + br + MB::rpp * i;
-      st.b[i] = *reinterpret_cast<const float4*>(C + (size_t)(t < eta ? t : 0) * R + rc);
-      st.kb[i] = t < eta && rok;
-    }
-  };
-  constexpr int ASZ = SKW * PA, BSZ = SKW * PB;  // floats of one LDS buffer of each operand
-  auto put = [&](const Buf& st, int buf) {
-    // nothing moves across: a select hoisted above this point would wait for the other buffer
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < MA::passes; ++i)
-      *reinterpret_cast<float4*>(&As[buf * ASZ + (ar + MA::rpp * i) * PA + ac]) = keep4(st.ka[i], st.a[i]);
-#pragma unroll
-    for (int i = 0; i < MB::passes; ++i)
-      *reinterpret_cast<float4*>(&Bs[buf * BSZ + (br + MB::rpp * i) * PB + bc]) = keep4(st.kb[i], st.b[i]);
-  };
-  // Two register buffers and two LDS buffers: stage s + 1 is stored to LDS while stage s's
-  // products run from the other buffer (one barrier a stage), and the loads of the stage after
-  // that are in flight meanwhile (the workgroup is alone on its CU, so no other workgroup covers
-  // its load latency). Stage j's loads go to register buffer j % 2, unconditionally (rows past
-  // the end are clamped and stored as zeros), so each store waits only for its own buffer.
+                                               int64_t j0, int r0, u4v* As, u4v* Bs,
+                                               WideAcc<TM, TN>& acc) {
+  static_assert(TM == 128 && OCT == 4 && NTW == 512, "a wave a row of A, four waves an operand");
+  const int tid = threadIdx.x, lane = tid & 63, wave = uniform(tid >> 6);
+  // waves 0-3: octet `wave` of A, columns 2 * lane; waves 4-7: C
+  const bool a_role = wave < 4;
+  const unsigned aoff = 4u * (unsigned)(j0 + 2 * lane < n ? 2 * lane : 0);
+  const RowPairs<TN> cp(wave - 4, lane, r0, R);
+  const float *Ac = A + j0, *Cc = C + r0;
   const int nst = (eta + SKW - 1) / SKW;
-  if (nst == 0) return;
-  Buf b0, b1;
-  load(0, b0);
-  load(SKW, b1);
-  put(b0, 0);
-  load(2 * SKW, b0);
-  __syncthreads();
-  for (int q = 0; 2 * q < nst; ++q) {
-    mma_stage_w<TM, TN>(As, 0, Bs, wm, wn, lane, acc);  // stage 2q
-    if (2 * q + 1 >= nst) break;
-    put(b1, 1);                                         // stage 2q + 1
-    load((2 * q + 3) * SKW, b1);
-    __syncthreads();
-    mma_stage_w<TM, TN>(As + ASZ, 0, Bs + BSZ, wm, wn, lane, acc);
-    if (2 * q + 2 < nst) {
-      put(b0, 0);  // stage 2q + 2
-      load((2 * q + 4) * SKW, b0);
-    }
-    __syncthreads();
-  }
+  using Buf = Pairs;
+  auto load_a = [&](int st, Buf& u) {
+    const int at = (st < nst ? st : nst - 1) * SKW + 8 * wave;  // (past the end: in range, and no bytes)
+    int rows[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) rows[q] = uniform(taus[at + q]);
+    const int left = uniform(eta - st * SKW - 8 * wave);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) u.f[q] = load_at(Ac + (int64_t)rows[q] * ld, aoff, unbounded_if(q, left));
+  };
+  auto put_a = [&](Buf& u, int buf) { put_pairs<TM>(As + buf * SplitTile<TM>::words, wave, 2 * lane, u); };
+  auto load_c = [&](int st, Buf& u) { cp.load(Cc, R, (int64_t)st * SKW, eta, u); };
+  auto put_c = [&](Buf& u, int buf) { put_pairs<TN>(Bs + buf * SplitTile<TN>::words, cp.oct, cp.col, u); };
+  roles_w<TM, TN, Buf>(a_role, cp.has, nst, As, Bs, wave >> 1, wave & 1, lane, acc, load_a, put_a, load_c, put_c);
 }
 
-template <int TM, int TN>
-__device__ __forceinline__ void zero_acc(f4 (&acc)[TM / (16 * WGM)][TN / (16 * WGN)]) {
-#pragma unroll
-  for (int i = 0; i < TM / (16 * WGM); ++i)
-#pragma unroll
-    for (int j = 0; j < TN / (16 * WGN); ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
-}
+// two neighbours, at any float
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));
+__device__ __forceinline__ void store2(float* p, float a, float b) { *reinterpret_cast<f2u*>(p) = f2u{a, b}; }
+__device__ __forceinline__ f2u load2(const float* p) { return *reinterpret_cast<const f2u*>(p); }
 
 }  // namespace
 
@@ -624,11 +738,8 @@ __global__ __launch_bounds__(NTW) void gemm_at_x_w(const float* __restrict__ A, 
                                                    const float* __restrict__ X, int R, float* __restrict__ Y,
                                                    int eta_pad, int64_t kspan, int gt, int gr, int S, int* status,
                                                    int64_t m, int64_t k) {
-  constexpr int LDR = SKW + 4, PB = TN + 16;
-  using MA = WideMap<SKW>;  // a row piece of SKW floats: 8 float4
-  using MB = WideMap<TN>;
-  __shared__ __align__(16) float Ar[2 * TM * LDR];
-  __shared__ __align__(16) float Bs[2 * SKW * PB];
+  __shared__ u4v As[2 * SplitTile<TM>::words];
+  __shared__ u4v Bs[2 * SplitTile<TN>::words];
   __shared__ int flag;
   if (m == 0 && any_fault(status, &flag)) return;
   const int st0 = status[0];  // used late, as in gemm_at_x
@@ -649,18 +760,21 @@ __global__ __launch_bounds__(NTW) void gemm_at_x_w(const float* __restrict__ A, 
   int64_t j_end = j_begin + kspan;
   if (j_end > n) j_end = n;
 
-  // A: thread -> row t0 + ar + MA::rpp * i (TM / MA::rpp rows), 4 columns at ac of the stage
-  constexpr int AP = TM / MA::rpp;
-  static_assert(AP * MA::rpp == TM && MB::passes >= 1 && MB::passes * MB::rpp == SKW, "whole passes");
-  const int ar = tid / MA::cpr, ac = (tid % MA::cpr) * 4;
-  const float* arow[AP];
+  // waves 0-3: X; waves 4-7: octet ao of rows t0 + ai and t0 + ai + 64 of A (four lanes read a row's 128
+  // bytes)
+  static_assert(TM == 128 && OCT == 4 && NTW == 512, "two rows a thread of four waves");
+  const int uwave = uniform(wave);
+  const bool a_role = uwave >= 4;
+  const RowPairs<TN> xp(uwave, lane, r0, R);
+  const int ao = tid % OCT, ai = tid % 256 / OCT;
+  const float* arow[2];
   int bad = 0;
 #pragma unroll
-  for (int i = 0; i < AP; ++i) {
-    const int t = t0 + ar + MA::rpp * i;
+  for (int i = 0; i < 2; ++i) {
+    const int t = t0 + ai + 64 * i;
     int row = t < eta ? tau[t] : 0;
     if (m > 0 && (row < 0 || (int64_t)row >= m)) { bad = 1; row = 0; }
-    arow[i] = A + (int64_t)row * ld;
+    arow[i] = A + (int64_t)row * ld + 8 * ao;
   }
   if (bad && st0 == 0) {
     set_status(status, ST_INDEX);
@@ -668,75 +782,46 @@ __global__ __launch_bounds__(NTW) void gemm_at_x_w(const float* __restrict__ A, 
   }
   // steps before k completed (status[1] only grows; a fault at step k records k as well)
   if (m > 0 && blockIdx.x == 0 && threadIdx.x == 0 && st0 == 0) atomicMax(status + 1, (int)k);
-  // X: thread -> rows br + MB::rpp * i of the stage, 4 columns at bc
-  const int br = tid / MB::cpr, bc = (tid % MB::cpr) * 4;
-  const bool rok = r0 + bc < R;
-  const int rc = rok ? r0 + bc : 0;
-  struct Buf {
-    float4 a[AP], b[MB::passes];
-    bool ka[AP], kb[MB::passes];
-  };
-  auto load = [&](int64_t jb, Buf& st) {
-    const int64_t c = jb + ac;
-#pragma unroll
-    for (int i = 0; i < AP; ++i) {
-      st.a[i] = *reinterpret_cast<const float4*>(arow[i] + (c < j_end ? c : 0));
-      st.ka[i] = c < j_end;
-    }
-#pragma unroll
-    for (int i = 0; i < MB::passes; ++i) {
-      const int64_t jj = jb + br + MB::rpp * i;
-      st.b[i] = *reinterpret_cast<const float4*>(X + (jj < j_end ? jj : 0) * R + rc);
-      st.kb[i] = jj < j_end && rok;
-    }
-  };
-  constexpr int ASZ = TM * LDR, BSZ = SKW * PB;  // floats of one LDS buffer of each operand
-  auto put = [&](const Buf& st, int buf) {
-    // nothing moves across: a select hoisted above this point would wait for the other buffer
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int i = 0; i < AP; ++i)
-      *reinterpret_cast<float4*>(&Ar[buf * ASZ + (ar + MA::rpp * i) * LDR + ac]) = keep4(st.ka[i], st.a[i]);
-#pragma unroll
-    for (int i = 0; i < MB::passes; ++i)
-      *reinterpret_cast<float4*>(&Bs[buf * BSZ + (br + MB::rpp * i) * PB + bc]) = keep4(st.kb[i], st.b[i]);
-  };
-  f4 acc[TM / (16 * WGM)][TN / (16 * WGN)];
-  zero_acc<TM, TN>(acc);
-  // two register buffers and two LDS buffers, one barrier a stage (as att_mainloop_w)
+  const float* Xc = X + r0;
   const int nst = j_end > j_begin ? (int)((j_end - j_begin + SKW - 1) / SKW) : 0;
-  if (nst > 0) {
-    Buf b0, b1;
-    load(j_begin, b0);
-    load(j_begin + SKW, b1);
-    put(b0, 0);
-    load(j_begin + 2 * SKW, b0);
-    __syncthreads();
-    for (int q = 0; 2 * q < nst; ++q) {
-      mma_stage_w<TM, TN>(Ar, 1, Bs, wm, wn, lane, acc);  // stage 2q
-      if (2 * q + 1 >= nst) break;
-      put(b1, 1);                                         // stage 2q + 1
-      load(j_begin + (int64_t)(2 * q + 3) * SKW, b1);
-      __syncthreads();
-      mma_stage_w<TM, TN>(Ar + ASZ, 1, Bs + BSZ, wm, wn, lane, acc);
-      if (2 * q + 2 < nst) {
-        put(b0, 0);  // stage 2q + 2
-        load(j_begin + (int64_t)(2 * q + 4) * SKW, b0);
+  using Buf = Pairs;  // A's: f[4 * i + 2 * h + (0, 1)] holds float4 h of row i
+  const int ncol = (int)(n - 4 - 8 * ao);
+  auto load_a = [&](int st, Buf& u) {
+    // columns outside the split meet zeros of X, whatever A holds there; past the row its last ones load
+    const int j = (int)j_begin + st * SKW;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 v = *reinterpret_cast<const float4*>(arow[i] + (j + 4 * h < ncol ? j + 4 * h : ncol));
+        u.f[4 * i + 2 * h] = make_float2(v.x, v.y);
+        u.f[4 * i + 2 * h + 1] = make_float2(v.z, v.w);
       }
-      __syncthreads();
+  };
+  auto put_a = [&](Buf& u, int buf) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float f[8] = {u.f[4 * i].x,     u.f[4 * i].y,     u.f[4 * i + 1].x, u.f[4 * i + 1].y,
+                          u.f[4 * i + 2].x, u.f[4 * i + 2].y, u.f[4 * i + 3].x, u.f[4 * i + 3].y};
+      put8<TM>(As + buf * SplitTile<TM>::words, ao, ai + 64 * i, f);
     }
-  }
-  // D layout: column lane%16, rows 4*(lane/16) + v
+  };
+  auto load_x = [&](int st, Buf& u) { xp.load(Xc, R, j_begin + (int64_t)st * SKW, j_end, u); };
+  auto put_x = [&](Buf& u, int buf) { put_pairs<TN>(Bs + buf * SplitTile<TN>::words, xp.oct, xp.col, u); };
+  WideAcc<TM, TN> acc;
+  acc.zero();
+  roles_w<TM, TN, Buf>(a_role, xp.has, nst, As, Bs, wm, wn, lane, acc, load_a, put_a, load_x, put_x);
+  // D layout: position lane%16, rows 4*(lane/16) + v; blocks 2j and 2j + 1 hold a column pair
   float* Ys = Y + (size_t)s * eta_pad * R;
 #pragma unroll
   for (int i = 0; i < TM / (16 * WGM); ++i)
 #pragma unroll
-    for (int j = 0; j < TN / (16 * WGN); ++j)
+    for (int j = 0; j < TN / (16 * WGN); j += 2)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int t = t0 + wm * (TM / WGM) + i * 16 + 4 * (lane >> 4) + v;
-        const int r = r0 + wn * (TN / WGN) + j * 16 + (lane & 15);
-        if (r < R) Ys[(size_t)t * R + r] = acc[i][j][v];
+        const int r = r0 + tile_col(wn * (TN / WGN) + j * 16 + (lane & 15));
+        if (r < R) store2(Ys + (size_t)t * R + r, acc.sum(i, j, v), acc.sum(i, j + 1, v));
       }
 }
 
@@ -750,9 +835,9 @@ __global__ __launch_bounds__(NTW) void gemm_att_w(const float* __restrict__ A, i
                                                   float* __restrict__ X, float lambda, float* __restrict__ Wp,
                                                   const int* status) {
   const int st0 = status[0];  // checked once the indices are staged, as in gemm_att_c_update
-  __shared__ __align__(16) float As[2 * SKW * (TM + 16)];
-  __shared__ __align__(16) float Bs[2 * SKW * (TN + 16)];
-  __shared__ int taus[kMaxTauLds];
+  __shared__ u4v As[2 * SplitTile<TM>::words];
+  __shared__ u4v Bs[2 * SplitTile<TN>::words];
+  __shared__ int taus[kMaxTauLds + SKW];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave >> 1, wn = wave & 1;
   const int64_t j0 = (int64_t)blockIdx.x * TM;
@@ -760,43 +845,48 @@ __global__ __launch_bounds__(NTW) void gemm_att_w(const float* __restrict__ A, i
   const int s2 = blockIdx.z, S2 = gridDim.z;
   const int tb0 = (int)((int64_t)s2 * eta / S2), tb1 = (int)((int64_t)(s2 + 1) * eta / S2);
   stage_tau(tau + tb0, tb1 - tb0, taus);
+  // (the stage that runs past the split reads its first row there; masked)
+  if (tid < SKW && tb1 > tb0) taus[tb1 - tb0 + tid] = tau[tb0];
   __syncthreads();
   if (st0) return;
   constexpr int BI = TM / (16 * WGM), BJ = TN / (16 * WGN);
+  // element (i, j, v) of the accumulators, j even: row jj of the output, columns r and r + 1 (j + 1)
+  auto row_of = [&](int i, int v) { return j0 + tile_col(wm * (TM / WGM) + i * 16 + 4 * (lane >> 4) + v); };
+  auto col_of = [&](int j) { return r0 + tile_col(wn * (TN / WGN) + j * 16 + (lane & 15)); };
   // the update's x* inputs load before the products (in flight under them), not after
-  float zin[UPDATE ? BI : 1][UPDATE ? BJ : 1][4];
+  f2u zin[UPDATE ? BI : 1][UPDATE ? BJ / 2 : 1][4];
   if constexpr (UPDATE) {
 #pragma unroll
     for (int i = 0; i < BI; ++i)
 #pragma unroll
-      for (int j = 0; j < BJ; ++j)
+      for (int j = 0; j < BJ; j += 2)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-          const int64_t jj = j0 + wm * (TM / WGM) + i * 16 + 4 * (lane >> 4) + v;
-          const int r = r0 + wn * (TN / WGN) + j * 16 + (lane & 15);
-          zin[i][j][v] = Zin[jj < n && r < R ? (size_t)jj * R + r : 0];
+          const int64_t jj = row_of(i, v);
+          const int r = col_of(j);
+          zin[i][j / 2][v] = load2(Zin + (jj < n && r < R ? (size_t)jj * R + r : 0));
         }
   }
-  f4 acc[BI][BJ];
-  zero_acc<TM, TN>(acc);
+  WideAcc<TM, TN> acc;
+  acc.zero();
   att_mainloop_w<TM, TN>(A, ld, n, taus, tb1 - tb0, C + (size_t)tb0 * R, R, j0, r0, As, Bs, acc);
   float* W = UPDATE ? nullptr : Wp + (size_t)s2 * n * R;
 #pragma unroll
   for (int i = 0; i < BI; ++i)
 #pragma unroll
-    for (int j = 0; j < BJ; ++j)
+    for (int j = 0; j < BJ; j += 2)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const int64_t jj = j0 + wm * (TM / WGM) + i * 16 + 4 * (lane >> 4) + v;
-        const int r = r0 + wn * (TN / WGN) + j * 16 + (lane & 15);
+        const int64_t jj = row_of(i, v);
+        const int r = col_of(j);
         if (jj < n && r < R) {
           const size_t o = (size_t)jj * R + r;
           if constexpr (UPDATE) {
-            const float z = zin[i][j][v] - acc[i][j][v];
-            Zout[o] = z;
-            X[o] = shrink(z, lambda);
+            const float z0 = zin[i][j / 2][v][0] - acc.sum(i, j, v), z1 = zin[i][j / 2][v][1] - acc.sum(i, j + 1, v);
+            store2(Zout + o, z0, z1);
+            store2(X + o, shrink(z0, lambda), shrink(z1, lambda));
           } else {
-            W[o] = acc[i][j][v];
+            store2(W + o, acc.sum(i, j, v), acc.sum(i, j + 1, v));
           }
         }
       }
@@ -875,13 +965,14 @@ static void launch_at_x(const MultiRhsArgs& a, const int32_t* tk, const float* X
                         hipStream_t stream) {
   if (a.tile == 128) {
     const int gt = a.eta_pad / 128;
-    if (a.R > 64) {
+    if (a.tn == 128) {
       const int gr = (a.R + 127) / 128;
       hipLaunchKernelGGL((gemm_at_x_w<128, 128>), dim3(gt * gr * a.S), dim3(NTW), 0, stream, a.A, a.ld, a.n, tk,
                          a.eta, X, a.R, a.Y, a.eta_pad, a.kspan, gt, gr, a.S, a.status, m, k);
     } else {
-      hipLaunchKernelGGL((gemm_at_x_w<128, 64>), dim3(gt * a.S), dim3(NTW), 0, stream, a.A, a.ld, a.n, tk, a.eta,
-                         X, a.R, a.Y, a.eta_pad, a.kspan, gt, 1, a.S, a.status, m, k);
+      const int gr = (a.R + 63) / 64;
+      hipLaunchKernelGGL((gemm_at_x_w<128, 64>), dim3(gt * gr * a.S), dim3(NTW), 0, stream, a.A, a.ld, a.n, tk,
+                         a.eta, X, a.R, a.Y, a.eta_pad, a.kspan, gt, gr, a.S, a.status, m, k);
     }
     return;
   }
@@ -896,7 +987,7 @@ static void launch_at_x(const MultiRhsArgs& a, const int32_t* tk, const float* X
 static void launch_att(const MultiRhsArgs& a, const int32_t* tk, const float* C, const float* zin, float* zout,
                        bool update, hipStream_t stream) {
   const unsigned gn = (unsigned)((a.n + 127) / 128), z = update ? 1u : (unsigned)a.S2;
-  if (a.R > 64 && !update) {
+  if (a.tn == 128 && !update) {
     const dim3 g(gn, (unsigned)((a.R + 127) / 128), z);
     hipLaunchKernelGGL((gemm_att_w<128, 128, false>), g, dim3(NTW), 0, stream, a.A, a.ld, a.n, tk, a.eta, C, a.R,
                        zin, zout, a.x, a.lambda, a.Wp, a.status);
