@@ -223,7 +223,7 @@ __global__ __launch_bounds__(kBrtThreads) void rska_batched_rt(const rsk_batch_i
     if (!join_group(region, pl.G, it.status_dev, join_ticks, sh)) continue;
     DenseArgs<float> a;
     fill_args(a, it, pl, region);
-    rt_run<kBrtThreads, kBrtPasses, kBrtCpl, 1, true, kBrtPfBytes>(a, rank, pl.cpl);
+    rt_run<kBrtThreads, kBrtPasses, kBrtCpl, kBrtPfBytes>(a, rank, pl.cpl);
     __syncthreads();  // the body's LDS is reused by the next ticket's system
   }
 }

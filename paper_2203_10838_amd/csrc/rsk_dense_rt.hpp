@@ -1,9 +1,8 @@
 // Dense RSKA, float32, register-tile step for the batched launch (rska_batched_rt).
 //
-// The step of the single-system register-tile kernel (rska_dense_rt in rsk_dense_rt.hip: same
-// lane layout, LDS prefetch of the next step's first slots, exchange protocol and summation
-// orders), written as a device function for a workgroup that solves one system of a batch after
-// another. What differs for a batched system (BATCH = true):
+// The step of the single-system register-tile kernel (rska_dense_rt in rsk_dense_rt_kernel.hpp: same
+// lane layout, LDS prefetch of the next step's first slots and exchange protocol), written as a device
+// function for a workgroup that solves one system of a batch after another. What differs:
 //  * ranks map to column slices in order (the ranks of a system are drawn from a ticket queue,
 //    so their XCDs are not known);
 //  * only the chunk slots of a lane that hold the system's columns (cplr <= CPL) and the passes
@@ -13,13 +12,16 @@
 //  * global memory is read through address-space-1 pointers (the pointers come from a
 //    descriptor in memory and would otherwise be FLAT loads, whose count also gates every LDS
 //    wait of the step);
-//  * a wave that reduces several rows polls their partial sums in one round trip when each lane
-//    holds one slice (at most 64 workgroups);
 //  * the issuing waves wait for their LDS prefetch with the count of HBM slot loads they issued
-//    after it, which varies with the system.
-// The single-system kernel keeps its own copy of the step: compiled from this function it ran
-// 6% slower on its headline shape (100000 x 20000, eta = 1024: 21.9 against 20.6 us per
-// iteration, same registers and LDS; the instruction schedule differs).
+//    after it, which varies with the system;
+//  * rows are reduced by the waves that do not issue the prefetch, and a small system's in one hop, a
+//    row a thread.
+//
+// What bounds it: a step's chain of latencies, 6.4 us for a workgroup's 17 KB of rows and 13 us for
+// 160 KB, of which HBM's share is 7 us. 512 systems of up to 8000 x 4000, 100 steps: 22.6 ms with the
+// indices fetched at the top of the step that needs them, the tile's bounds in vector registers (each
+// of its branches a mask), a prefetch loop that worked out each slot by itself (2.7 us where it had
+// next to nothing to load) and two hops for every system of more than 32 rows; 15.8 without these.
 #pragma once
 #include "rsk_device.hpp"
 #include "rsk_kernels.hpp"
@@ -43,39 +45,16 @@ __device__ __forceinline__ float dpp(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, false));
 }
 
-// Sum over aligned groups of RL adjacent lanes (RL = 16: a DPP row; 8: half a
-// row); every lane of the group gets the sum.
-template <int RL>
-__device__ __forceinline__ float lanes_sum(float v) {
-  if constexpr (RL == 16) {
-    v += dpp<0x128>(v);  // row_ror:8
-    v += dpp<0x124>(v);  // row_ror:4
-    v += dpp<0x122>(v);  // row_ror:2
-    v += dpp<0x121>(v);  // row_ror:1
-  } else {
-    static_assert(RL == 8, "row groups of 16 or 8 lanes");
-    v += dpp<0xB1>(v);   // quad_perm [1,0,3,2]
-    v += dpp<0x4E>(v);   // quad_perm [2,3,0,1]
-    v += dpp<0x141>(v);  // row_half_mirror: quad 0 <-> quad 1 of each half row
-  }
+// Sum over the 16 lanes of a DPP row; every lane gets it.
+__device__ __forceinline__ float row_lanes_sum(float v) {
+  v += dpp<0x128>(v);  // row_ror:8
+  v += dpp<0x124>(v);  // row_ror:4
+  v += dpp<0x122>(v);  // row_ror:2
+  v += dpp<0x121>(v);  // row_ror:1
   return v;
 }
 
 }  // namespace
-
-// Loads of the step: through the global address space for a batched system (its pointers come
-// from a descriptor in memory and would otherwise be FLAT, whose count also gates every LDS wait);
-// plain loads for one system (kernel-argument pointers are global already).
-template <bool GLOBAL, typename T>
-__device__ __forceinline__ T ld(const T* p) {
-  if constexpr (GLOBAL) return load_global(p);
-  else return *p;
-}
-template <bool GLOBAL>
-__device__ __forceinline__ float4 ld4(const float* p) {
-  if constexpr (GLOBAL) return load_global_f4(p);
-  else return *reinterpret_cast<const float4*>(p);
-}
 
 // s_waitcnt until at most n vector memory loads of the wave are outstanding (n wave-uniform,
 // 0 <= n <= N): the count is an immediate, so uniform branches pick the constant.
@@ -89,62 +68,46 @@ __device__ __forceinline__ void wait_vm_at_most(int n) {
   }
 }
 
-// Global memory is read through address-space-1 pointers: a pointer taken from a batch
-// descriptor is otherwise accessed with FLAT instructions, which also count against the LDS
-// counter, so that every LDS wait of the step would wait for the row loads in flight.
-//
-// One solve on the register tile. g is this workgroup's rank among the a.G that solve the
-// system (its block index for one system). BATCH (a system of a batched launch): ranks map to
-// slices in order, only the first cplr chunk slots of a lane and the passes that hold rows of
-// the step are loaded and used, and a last chunk that reaches past n (n % 4 != 0, rows padded
-// to a multiple of 4 floats) has its padding masked to zero.
-// PF_BYTES: LDS for the next step's prefetched slots (147456: one workgroup a CU).
-template <int NT, int RP, int CPL, int RG, bool BATCH, int PF_BYTES = 147456>
-__device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const int cplr) {
+// One solve on the register tile. g is this workgroup's rank among the a.G that solve the system, its
+// columns slice g, cplr the chunk slots of a lane that hold columns of the widest slice.
+// PF_BYTES: LDS for the next step's prefetched slots.
+template <int NT, int RP, int CPL, int PF_BYTES>
+__device__ __forceinline__ void rt_run(const DenseArgs<float>& a, const int g, const int cplr) {
   constexpr int kRtThreads = NT;
   constexpr int kRtWaves = NT / 64;
-  constexpr int RL = 16 / RG;                     // rows a wave holds per pass
-  constexpr int CL = 4 * RG;                      // lanes of one row
+  constexpr int RL = 16;                          // rows a wave holds per pass
+  constexpr int CL = 4;                           // lanes of one row
   constexpr int kRtRowsPerPass = kRtWaves * RL;
   constexpr int SW = 4 * CL * CPL;                // floats of the widest slice
-  constexpr int kOwnMax = kRtOwnMax;              // rows one wave reduces per step
-  constexpr int kPollWaves = RG > 1 ? (SW + 63) / 64 : 0;  // waves holding the third hop's pollers
-  static_assert(kPollWaves <= kRtWaves / 2, "the pollers of the third hop do not issue the LDS prefetch");
+  // the waves that reduce rows (the others issue the LDS prefetch: a wave's loads return in order, so an
+  // issuing wave would see the partials it polls only after its share of the prefetch), and rows a wave
+  constexpr int kOwners = kRtWaves / 2;
+  constexpr int kOwnMax = kRtOwnMax * kRtWaves / kOwners;
+  static_assert(64 * kOwners == kBrtOneHopRows, "one hop: a row an owner thread");
+  static_assert(SW <= NT, "the slice's columns, one a thread");
   __shared__ float4 xs4[CL * CPL];                // x* slice
   __shared__ float4 xv4[CL * CPL];                // x slice
   __shared__ float4 red[kRtWaves][CL * CPL];      // per-wave column sums
   __shared__ float cs[RP * kRtRowsPerPass];        // step coefficients
   __shared__ double mon[2 * kRtWaves + 2];
   __shared__ int orflag[2];  // step-parity flag words of the block OR
-  __shared__ int hop3_bad[2];  // step-parity: a non-finite sum of the slice's update parts
   // next-step tile slots prefetched into LDS: (p, r) with s = p * CPL + r < NPF; LDS slot s * NT + tid
   // holds tile[p][r] of thread tid. PL passes hold prefetched slots.
   constexpr int kPfBudget = PF_BYTES / (NT * 16);
-  // (1024-thread tiles wider than 12 slots leave no registers for the prefetch loop)
-  constexpr int NPF = (NT == 1024 && RP * CPL > 12) ? 0 : (RP * CPL < kPfBudget ? RP * CPL : kPfBudget);
+  constexpr int NPF = RP * CPL < kPfBudget ? RP * CPL : kPfBudget;
   constexpr int PL = (NPF + CPL - 1) / CPL;
-  // s_waitcnt immediate with vmcnt = kHbmSlots (bits 3:0 and 15:14), expcnt and lgkmcnt not waited on
   constexpr int kHbmSlots = RP * CPL - NPF;
   static_assert(kHbmSlots < 64, "vmcnt holds at most 63");
-  constexpr int kWaitPrefetch = (kHbmSlots & 15) | ((kHbmSlots >> 4) << 14) | (7 << 4) | (15 << 8);
-  __shared__ float4 pf[NPF > 0 ? NPF * NT : 1];
-  __shared__ int nrow[PL > 0 ? PL * kRtRowsPerPass : 1];  // rows of the passes holding prefetched slots
+  __shared__ float4 pf[NPF * NT];
+  __shared__ int nrow[PL * kRtRowsPerPass];  // rows of the passes holding prefetched slots
 
   const int G = a.G, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int eta = a.eta;
   const int sl = lane / RL, ri = lane % RL;
 
-  // column slice s of C = G / RG and row group h (the RG workgroups of a slice are adjacent in
-  // the XCD-aware order); the group's rows of a step are h * etaR .. h * etaR + etaH - 1
-  const int C = G / RG;
-  const int sx = BATCH ? g : xcd_slice(g, G);
-  const int s = sx / RG, h = sx % RG;
-  const int etaR = (eta + RG - 1) / RG;
-  const int hr0 = h * etaR;
-  const int etaH = hr0 >= eta ? 0 : (eta - hr0 < etaR ? eta - hr0 : etaR);
   // slice in 4-chunk (64-byte) units
   const int64_t nunits = (a.nchunks + 3) / 4;
-  const int64_t u0 = (int64_t)s * nunits / C, u1 = (int64_t)(s + 1) * nunits / C;
+  const int64_t u0 = (int64_t)g * nunits / G, u1 = (int64_t)(g + 1) * nunits / G;
   const int64_t q0 = u0 * 4;
   int64_t q1 = u1 * 4;
   if (q1 > a.nchunks) q1 = a.nchunks;
@@ -152,23 +115,23 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
   const int64_t c0 = q0 * 4;
   // last chunk of the row reachable from this slice (clamp target)
   const int qlast = (int)(a.nchunks - 1 - q0);
-  // batched systems: a loaded chunk at or past qlast is the row's last one, whose elements at or
-  // past n % 4 are row padding (kept out of the dots and the update)
-  const int nrem = BATCH ? (int)(a.n & 3) : 0;
-  // chunk slot r of a lane, pass p of wave wv: loaded and used (a batched system may use fewer
-  // slots than CPL, and fewer passes than RP)
-  auto son = [&](int r) { return !BATCH || r < cplr; };
-  auto pon = [&](int p, int wv) { return !BATCH || p * kRtRowsPerPass + RL * wv < etaH; };
+  // a loaded chunk at or past qlast is the row's last one, whose elements at or past n % 4 are row
+  // padding (kept out of the dots and the update)
+  const int nrem = (int)(a.n & 3);
+  // chunk slots r < cpl of a lane and passes p < np of the wave are loaded and used (both in scalar
+  // registers: branches, not masks)
+  auto passes_of = [&](int wv) { return (eta - RL * wv + kRtRowsPerPass - 1) / kRtRowsPerPass; };
+  int cpl = __builtin_amdgcn_readfirstlane(cplr), np = __builtin_amdgcn_readfirstlane(passes_of(wave));
+  auto son = [&](int r) { return r < cpl; };
+  auto pon = [&](int p) { return p < np; };
   int nhbm = 0;  // next-step slots this wave loads from HBM (not from the LDS prefetch)
-  if constexpr (BATCH) {
 #pragma unroll
-    for (int p = 0; p < RP; ++p)
+  for (int p = 0; p < RP; ++p)
 #pragma unroll
-      for (int r = 0; r < CPL; ++r)
-        if (p * CPL + r >= NPF && son(r) && pon(p, wave)) ++nhbm;
-  }
+    for (int r = 0; r < CPL; ++r)
+      if (p * CPL + r >= NPF && son(r) && pon(p)) ++nhbm;
   auto mask_tail = [&](float4& v, int q) {
-    if (BATCH && nrem && q >= qlast) {
+    if (nrem && q >= qlast) {
       if (nrem < 2) v.y = 0.f;
       if (nrem < 3) v.z = 0.f;
       v.w = 0.f;
@@ -177,15 +140,15 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
   float* xs = reinterpret_cast<float*>(xs4);
   float* xv = reinterpret_cast<float*>(xv4);
 
-  // group rows this workgroup reduces: a contiguous block (two hops) or all (one hop)
-  const int per = a.two_hop ? (etaR + C - 1) / C : etaR;
-  const int ot0 = a.two_hop ? s * per : 0;
-  const int ot1 = (ot0 + per < etaH) ? ot0 + per : etaH;
+  // rows this workgroup reduces: a contiguous block (two hops) or all (one hop)
+  const int per = a.two_hop ? (eta + G - 1) / G : eta;
+  const int ot0 = a.two_hop ? g * per : 0;
+  const int ot1 = (ot0 + per < eta) ? ot0 + per : eta;
 
-  if (tid < 2) orflag[tid] = hop3_bad[tid] = 0;
+  if (tid < 2) orflag[tid] = 0;
   for (int j = tid; j < SW; j += kRtThreads) {
     const int64_t c = c0 + j;
-    const float z = (a.warm && j < wq * 4 && c < a.n) ? ld<BATCH>(a.x_star + c) : 0.f;
+    const float z = (a.warm && j < wq * 4 && c < a.n) ? load_global(a.x_star + c) : 0.f;
     xs[j] = z;
     xv[j] = shrink(z, a.lambda);
   }
@@ -196,53 +159,48 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
   // the first is checked: a load inside a branch is waited for at once, one
   // round trip each.
   int rowi[RP];
-  float ob[kOwnMax], orn[kOwnMax];
+  float ob = 0.f, orn = 1.f;  // lane j: those of the wave's row j
   int lerr = 0;
-  auto fetch_rows = [&](int64_t k, int (&ri_out)[RP], int& err) {
+  // raw indices of the lane's rows of step k (the next one's, fetched during the step before it)
+  int iraw[RP], oi = 0;
+  auto fetch_rows = [&](int64_t k) {
     const int32_t* tk = a.idx + k * (int64_t)eta;
 #pragma unroll
     for (int p = 0; p < RP; ++p) {
       const int t = p * kRtRowsPerPass + RL * wave + ri;
-      ri_out[p] = ld<BATCH>(tk + (t < etaH ? hr0 + t : 0));
+      iraw[p] = load_global(tk + (t < eta ? t : 0));
     }
-    int xo[RG > 1 ? RP : 1];
-    if constexpr (RG > 1) {
-#pragma unroll
-      for (int p = 0; p < RP; ++p) {
-        const int t = p * kRtRowsPerPass + RL * wave + ri;
-        const int tt = (1 - h) * etaR + t;
-        xo[p] = ld<BATCH>(tk + ((t < etaR && tt < eta) ? tt : 0));
-      }
-    }
+  };
+  auto check_rows = [&](int (&ri_out)[RP], int& err) {
 #pragma unroll
     for (int p = 0; p < RP; ++p) {
       const int t = p * kRtRowsPerPass + RL * wave + ri;
-      int i = ri_out[p];
-      if (t >= etaH) i = -1;
+      int i = iraw[p];
+      if (t >= eta) i = -1;
       else if (i < 0 || (int64_t)i >= a.m) { err = ST_INDEX; i = -1; }
       ri_out[p] = i;
-      if constexpr (RG > 1) {
-        // the other group's rows are checked too: every workgroup stops at the same step
-        if (xo[p] < 0 || (int64_t)xo[p] >= a.m) err = ST_INDEX;
-      }
     }
   };
-  auto fetch_owned = [&](int64_t k) {
-    const int32_t* tk = a.idx + k * (int64_t)eta + hr0;
-#pragma unroll
-    for (int j = 0; j < kOwnMax; ++j) {
-      const int t = ot0 + wave + kRtWaves * j;
-      ob[j] = 0.f;
-      orn[j] = 1.f;
-      if (lane == 0 && t < ot1) {
-        const int i = ld<BATCH>(tk + t);
-        if (i >= 0 && (int64_t)i < a.m) { ob[j] = ld<BATCH>(a.b + i); orn[j] = weighted_rn(a.r2, a.row_w, i); }
-      }
-    }
+  // Two hops: wave w < kOwners reduces rows tw + kOwners * j < ot1, lane j finishing row j. One hop: the
+  // owner waves' threads one row each (eta <= 64 kOwners), every slice's partial by the thread itself.
+  const int tw = wave < kOwners ? ot0 + wave : ot1;
+  int nown = a.two_hop && tw < ot1 ? (ot1 - tw + kOwners - 1) / kOwners : 0;
+  if (nown > kOwnMax) nown = kOwnMax;
+  const bool omine = a.two_hop ? lane < nown : wave < kOwners && tid < eta;
+  const int orow = omine ? (a.two_hop ? tw + kOwners * lane : tid) : 0;
+  auto owned_index = [&](int64_t k) { return load_global(a.idx + k * (int64_t)eta + orow); };
+  auto owned_inputs = [&](int i, float& b, float& rn) {
+    const int ic = i >= 0 && (int64_t)i < a.m ? i : 0;  // (a bad index stops its step before they are used)
+    b = load_global(a.b + ic);
+    rn = weighted_rn(a.r2, a.row_w, ic);
   };
   if (a.K > 0) {
-    fetch_rows(0, rowi, lerr);
-    fetch_owned(0);
+    fetch_rows(0);
+    owned_inputs(owned_index(0), ob, orn);
+    check_rows(rowi, lerr);
+    const int64_t k1 = a.K > 1 ? 1 : 0;
+    fetch_rows(k1);
+    oi = owned_index(k1);
   }
   int64_t k_done = 0;
   int stop_code = 0;
@@ -253,35 +211,33 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
   // tile slot (p, r) of each of its 64 lanes; lane l of the issuing wave stands for lane l of
   // wave j, so the 64 x 16 B that one global_load_lds writes are the 64 consumers' slots in order.
   auto publish_rows = [&](const int (&rows)[RP]) {
-    if constexpr (NPF > 0) {
 #pragma unroll
-      for (int p = 0; p < PL; ++p)
-        if (sl == 0) nrow[p * kRtRowsPerPass + RL * wave + ri] = rows[p];
-    }
+    for (int p = 0; p < PL; ++p)
+      if (sl == 0) nrow[p * kRtRowsPerPass + RL * wave + ri] = rows[p];
   };
   auto issue_prefetch = [&]() {
-    if constexpr (NPF > 0) {
-      if (wave >= kRtWaves / 2) {
-        for (int I = wave - kRtWaves / 2; I < NPF * kRtWaves; I += kRtWaves / 2) {
-          const int j = I % kRtWaves, sp = I / kRtWaves, r = sp % CPL, p = sp / CPL;
-          if (!son(r) || !pon(p, j)) continue;
-          const int row = nrow[p * kRtRowsPerPass + RL * j + ri];
-          const int q = sl + CL * r;
-          const float* gp = a.A + (int64_t)(row < 0 ? 0 : row) * a.ld + c0 + 4 * (q < qlast ? q : qlast);
-          __builtin_amdgcn_global_load_lds(gp, (__attribute__((address_space(3))) void*)&pf[(p * CPL + r) * NT + 64 * j],
-                                           16, 0, 0);
-        }
+    if (wave < kOwners) return;
+    // (pass, consumer wave) pairs over the issuing waves
+    for (int I = wave - kOwners; I < PL * kRtWaves; I += kRtWaves - kOwners) {
+      const int j = I % kRtWaves, p = I / kRtWaves;
+      if (p >= passes_of(j)) continue;
+      const int row = nrow[p * kRtRowsPerPass + RL * j + ri];
+      const float* rp = a.A + (int64_t)(row < 0 ? 0 : row) * a.ld + c0;
+      const int rn = NPF - p * CPL < cpl ? NPF - p * CPL : cpl;
+      for (int r = 0; r < rn; ++r) {
+        const int q = sl + CL * r;
+        __builtin_amdgcn_global_load_lds(rp + 4 * (q < qlast ? q : qlast),
+                                         (__attribute__((address_space(3))) void*)&pf[(p * CPL + r) * NT + 64 * j], 16,
+                                         0, 0);
       }
     }
   };
-  if constexpr (NPF > 0) {
-    if (!stop_code && a.K > 0) {
-      publish_rows(rowi);
-      __syncthreads();
-      issue_prefetch();
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-    }
+  if (!stop_code && a.K > 0) {
+    publish_rows(rowi);
+    __syncthreads();
+    issue_prefetch();
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
   }
 
   // The step's tile. Slots p * CPL + r < NPF come from the LDS prefetch; the others load from
@@ -291,13 +247,13 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
   if (!stop_code && a.K > 0) {
 #pragma unroll
     for (int p = 0; p < RP; ++p) {
-      if (!pon(p, wave)) continue;
+      if (!pon(p)) continue;
       const float* rowp = a.A + (int64_t)(rowi[p] < 0 ? 0 : rowi[p]) * a.ld + c0;
 #pragma unroll
       for (int r = 0; r < CPL; ++r) {
         if (p * CPL + r < NPF || !son(r)) continue;
         const int q = sl + CL * r;  // clamped into the row: past the slice it meets x = 0
-        tile[p][r] = ld4<BATCH>(rowp + 4 * (q < qlast ? q : qlast));
+        tile[p][r] = load_global_f4(rowp + 4 * (q < qlast ? q : qlast));
       }
     }
   }
@@ -309,8 +265,11 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
     int tidl = threadIdx.x;
     asm volatile("" : "+v"(tidl));
     const int tid = tidl, lane = tidl & 63, wave = tidl >> 6, sl = lane / RL, ri = lane % RL;
+    int cpv = cplr, npv = passes_of(wave);
+    asm volatile("" : "+v"(cpv), "+v"(npv));
+    cpl = __builtin_amdgcn_readfirstlane(cpv);
+    np = __builtin_amdgcn_readfirstlane(npv);
     const unsigned tag = (unsigned)(k + 1);
-    const float ak = a.alpha_k ? ld<BATCH>(a.alpha_k + k) : a.alpha;
     u64* xP = a.xP + (size_t)(k & 1) * G * eta;
     const bool has_next = k + 1 < a.K;
 
@@ -318,17 +277,16 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
     for (int p = 0; p < PL; ++p)
 #pragma unroll
       for (int r = 0; r < CPL; ++r)
-        if (p * CPL + r < NPF && son(r) && pon(p, wave)) tile[p][r] = pf[(p * CPL + r) * NT + tid];
+        if (p * CPL + r < NPF && son(r) && pon(p)) tile[p][r] = pf[(p * CPL + r) * NT + tid];
     int rown[RP];
 #pragma unroll
     for (int p = 0; p < RP; ++p) rown[p] = -1;
     int nerr = 0;
-    if (has_next) fetch_rows(k + 1, rown, nerr);
 
     // partial dots, published pass by pass
 #pragma unroll
     for (int p = 0; p < RP; ++p) {
-      if (!pon(p, wave)) continue;
+      if (!pon(p)) continue;
       float acc = 0.f;
 #pragma unroll
       for (int r = 0; r < CPL; ++r) {
@@ -339,70 +297,82 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
 #pragma unroll
       for (int o = RL; o < 64; o <<= 1) acc += __shfl_xor(acc, o);
       const int t = p * kRtRowsPerPass + RL * wave + ri;
-      if (sl == 0 && t < etaH) put_tagged(&xP[(size_t)s * eta + hr0 + t], acc, tag);
+      if (sl == 0 && t < eta) put_tagged(&xP[(size_t)g * eta + t], acc, tag);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (NPF > 0) {
+    // b and ||a||^2 of the next step's owned rows and the indices of the step after it, under this
+    // step's exchange
+    float obn = 0.f, ornn = 1.f;
+    if (has_next) {
       // every wave has consumed its LDS slots (the dots used them): the next step's may land
-      if (has_next) {
-        publish_rows(rown);
-        __syncthreads();
-        issue_prefetch();
-      }
+      check_rows(rown, nerr);
+      publish_rows(rown);
+      __syncthreads();
+      issue_prefetch();
+      if (wave < kOwners) owned_inputs(oi, obn, ornn);
+      const int64_t k2 = k + 2 < a.K ? k + 2 : a.K - 1;
+      fetch_rows(k2);
+      oi = owned_index(k2);
     }
     int bad = 0;
-    // reduce the owned rows over the C slices; c_t = (alpha/eta)(r_t - b)/||a||^2
-    auto own_coef = [&](int j, int t, float sum) {
-      sum = wave_sum(sum);
-      if (lane == 0) {
-        float c;
-        const float rn = orn[j];
-        if (rn == 0.f) { c = NAN; set_status(a.status, ST_ZERO_ROW); }
-        else c = (ak / (float)eta) * (sum - ob[j]) / rn;
-        if (a.two_hop) {
-          put_tagged(&a.xC[hr0 + t], c, tag);
-        } else {
-          cs[t] = c;
-          bad |= !isfinite(c);
+    // reduce the owned rows over the slices; lane j: c_t = (alpha/eta)(r_t - b)/||a||^2 of row j
+    float osum = 0.f;
+    if (!a.two_hop) {
+      if (omine) {
+        constexpr int kN = 8;
+        for (int s0 = 0; s0 < G; s0 += kN) {
+          float v[kN];
+          wait_tagged_batch(&xP[(size_t)s0 * eta + orow], (size_t)eta, G - s0 < kN ? G - s0 : kN, tag, v, lerr);
+#pragma unroll
+          for (int i = 0; i < kN; ++i) osum += v[i];
         }
       }
-    };
-    if (BATCH && C <= 64) {
-      // one slice a lane (a batched system): the wave's rows (kRtWaves apart) are polled
-      // together, one round trip for all of them (the same sums as row by row)
-      const int tw = ot0 + wave;
-      int nown = tw < ot1 ? (ot1 - tw + kRtWaves - 1) / kRtWaves : 0;
-      if (nown > kOwnMax) nown = kOwnMax;
+    } else if (G <= 64) {
+      // one slice a lane: the wave's rows are polled together, one round trip for all of them
       float v[kOwnMax];
-      wait_tagged_batch(&xP[(size_t)lane * eta + hr0 + (nown ? tw : 0)], kRtWaves, lane < C ? nown : 0, tag, v,
-                        lerr);
+      wait_tagged_batch(&xP[(size_t)lane * eta + (nown ? tw : 0)], kOwners, lane < G ? nown : 0, tag, v, lerr);
 #pragma unroll
       for (int j = 0; j < kOwnMax; ++j) {
-        const int t = tw + kRtWaves * j;
-        if (t < ot1) own_coef(j, t, v[j]);
+        if (j < nown) {
+          const float sum = wave_sum(v[j]);
+          if (lane == j) osum = sum;
+        }
       }
     } else {
 #pragma unroll
       for (int j = 0; j < kOwnMax; ++j) {
-        const int t = ot0 + wave + kRtWaves * j;
+        const int t = tw + kOwners * j;
         if (t < ot1) {
           float v[kMaxG / 64];
-          wait_tagged_batch(&xP[(size_t)lane * eta + hr0 + t], (size_t)64 * eta, (C - lane + 63) / 64, tag, v, lerr);
+          wait_tagged_batch(&xP[(size_t)lane * eta + t], (size_t)64 * eta, (G - lane + 63) / 64, tag, v, lerr);
           float sum = 0.f;
 #pragma unroll
           for (int i = 0; i < kMaxG / 64; ++i) sum += v[i];
-          own_coef(j, t, sum);
+          sum = wave_sum(sum);
+          if (lane == j) osum = sum;
         }
       }
     }
-    if (has_next) fetch_owned(k + 1);
+    if (omine) {
+      float c;
+      if (orn == 0.f) { c = NAN; set_status(a.status, ST_ZERO_ROW); }
+      else c = (a.alpha / (float)eta) * (osum - ob) / orn;
+      if (a.two_hop) {
+        put_tagged(&a.xC[orow], c, tag);
+      } else {
+        cs[orow] = c;
+        bad |= !isfinite(c);
+      }
+    }
+    ob = obn;
+    orn = ornn;
     if (a.two_hop && tid < kRtRowsPerPass) {
       float v[RP];
-      wait_tagged_batch(&a.xC[hr0 + tid], kRtRowsPerPass, (etaH - tid + kRtRowsPerPass - 1) / kRtRowsPerPass, tag,
+      wait_tagged_batch(&a.xC[tid], kRtRowsPerPass, (eta - tid + kRtRowsPerPass - 1) / kRtRowsPerPass, tag,
                         v, lerr);
 #pragma unroll
       for (int i = 0; i < RP; ++i)
-        if (tid + kRtRowsPerPass * i < etaH) {
+        if (tid + kRtRowsPerPass * i < eta) {
           cs[tid + kRtRowsPerPass * i] = v[i];
           bad |= !isfinite(v[i]);
         }
@@ -418,116 +388,78 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
     if (flag) atomicOr(&orflag[k & 1], flag);
     __syncthreads();
     const int fl = orflag[k & 1];
-    if (tid == 0) orflag[(k + 1) & 1] = hop3_bad[(k + 1) & 1] = 0;
+    if (tid == 0) orflag[(k + 1) & 1] = 0;
     if (fl & 1) { stop_code = ST_ABORTED; break; }
-    if (fl & 2) {
-      if constexpr (RG > 1) {
-        // the other group of the slice (whose coefficients may be finite) takes a NaN update
-        // part from this one and stops at the end of this step
-        if (tid < 4 * wq)
-          put_tagged(&a.xU[(((size_t)(k & 1) * C + s) * RG + h) * SW + tid], __builtin_nanf(""), tag);
-      }
-      stop_code = ST_NONFINITE;
-      break;
-    }
+    if (fl & 2) { stop_code = ST_NONFINITE; break; }
     const int next_bad = fl & 4;
 
-    // transposed update: per chunk slot, sum over own rows, then the RL lanes
+    // transposed update: per chunk slot, sum over own rows, then the 16 lanes
     // holding that chunk, then the waves
     float cp[RP];
 #pragma unroll
     for (int p = 0; p < RP; ++p) {
       const int t = p * kRtRowsPerPass + RL * wave + ri;
-      cp[p] = t < etaH ? cs[t] : 0.f;
+      cp[p] = t < eta ? cs[t] : 0.f;
     }
     const bool load_next = has_next && !next_bad;
-    if (a.y && s == 0)
-      for (int t = tid; t < etaH; t += kRtThreads) atomicAdd(&a.y[a.idx[k * (int64_t)eta + hr0 + t]], -cs[t]);
 #pragma unroll
     for (int r = 0; r < CPL; ++r) {
       if (!son(r)) continue;
       float4 d = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
       for (int p = 0; p < RP; ++p) {
-        if (!pon(p, wave)) continue;
+        if (!pon(p)) continue;
         d.x += cp[p] * tile[p][r].x;
         d.y += cp[p] * tile[p][r].y;
         d.z += cp[p] * tile[p][r].z;
         d.w += cp[p] * tile[p][r].w;
       }
-      d.x = lanes_sum<RL>(d.x);
-      d.y = lanes_sum<RL>(d.y);
-      d.z = lanes_sum<RL>(d.z);
-      d.w = lanes_sum<RL>(d.w);
+      d.x = row_lanes_sum(d.x);
+      d.y = row_lanes_sum(d.y);
+      d.z = row_lanes_sum(d.z);
+      d.w = row_lanes_sum(d.w);
       if (ri == 0) red[wave][sl + CL * r] = d;
     }
     // the tile is used up: the next step's HBM slots load now, row by row (a row's chunks issued
-    // back to back keep the DRAM pages open), and stay in flight across the plain barriers. The
-    // waves that poll the third hop issue theirs after it: a poll waits for all of its wave's loads.
-    auto load_tile = [&]() {
+    // back to back keep the DRAM pages open), and stay in flight across the plain barriers
+    if (load_next) {
 #pragma unroll
       for (int p = 0; p < RP; ++p) {
-        if (!pon(p, wave)) continue;
+        if (!pon(p)) continue;
         const float* rowp = a.A + (int64_t)(rown[p] < 0 ? 0 : rown[p]) * a.ld + c0;
 #pragma unroll
         for (int r = 0; r < CPL; ++r) {
           if (p * CPL + r < NPF || !son(r)) continue;
           const int q = sl + CL * r;
-          tile[p][r] = ld4<BATCH>(rowp + 4 * (q < qlast ? q : qlast));
+          tile[p][r] = load_global_f4(rowp + 4 * (q < qlast ? q : qlast));
         }
       }
-    };
-    if (load_next && wave >= kPollWaves) load_tile();
+    }
     __syncthreads();  // publishes red[]
     if (tid < 4 * wq) {  // chunks past the slice carry clamped data: discarded
-      const int q = tid >> 2, e = tid & 3;
       float dsum = 0.f;
-      for (int w = 0; w < kRtWaves; ++w) {
-        const float4 v = red[w][q];
-        dsum += e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
-      }
-      if constexpr (RG > 1) {
-        // third hop: the slice's RG groups add their parts in group order, so every copy of the
-        // slice gets the same x (the next step's HBM loads are in flight meanwhile)
-        u64* xU = a.xU + ((size_t)(k & 1) * C + s) * RG * SW;
-        put_tagged(&xU[(size_t)h * SW + tid], dsum, tag);
-        float tot = 0.f;
 #pragma unroll
-        for (int hh = 0; hh < RG; ++hh) tot += hh == h ? dsum : wait_tagged<float>(&xU[(size_t)hh * SW + tid], tag, lerr);
-        if (lerr) set_status(a.status, ST_ABORTED);
-        if (!isfinite(tot)) atomicOr(&hop3_bad[k & 1], 1);
-        dsum = tot;
-      }
+      for (int w = 0; w < kRtWaves; ++w) dsum += reinterpret_cast<const float*>(red[w])[tid];
       const float z = xs[tid] - dsum;
       xs[tid] = z;
       xv[tid] = shrink(z, a.lambda);
     }
-    if constexpr (RG > 1) {
-      if (load_next && wave < kPollWaves) load_tile();
-    }
     k_done = k + 1;
-    if constexpr (NPF > 0) {
-      // the LDS prefetch has landed before the barrier: the only loads this wave issued after
-      // it are the update's kHbmSlots next-step slots (older ones are done at vmcnt <= kHbmSlots)
-      if (wave >= kRtWaves / 2) {
-        if (!load_next) __builtin_amdgcn_s_waitcnt(0);
-        else if constexpr (BATCH) wait_vm_at_most<kHbmSlots>(nhbm);  // this wave issued nhbm of them
-        else __builtin_amdgcn_s_waitcnt(kWaitPrefetch);
-      }
+    // the LDS prefetch has landed before the barrier: the wave issued at least nhbm loads after it
+    // (older ones are done at vmcnt <= nhbm)
+    if (wave >= kOwners) {
+      if (!load_next) __builtin_amdgcn_s_waitcnt(0);
+      else wait_vm_at_most<kHbmSlots>(nhbm);
     }
     __syncthreads();
-    if constexpr (RG > 1) {
-      // a group that stopped on a non-finite coefficient sent NaN parts: every copy stops here
-      if (hop3_bad[k & 1]) { stop_code = ST_NONFINITE; break; }
-    }
 
     if (a.xref && a.check_every > 0 && (k + 1) % a.check_every == 0) {
       const unsigned mtag = (unsigned)((k + 1) / a.check_every);
       double e2 = 0.0, r2s = 0.0;
       for (int j = tid; j < wq * 4; j += kRtThreads) {
         const int64_t c = c0 + j;
-        if (c < a.n && h == 0) {  // one copy of each slice counts
-          const double rf = (double)ld<BATCH>(a.xref + c);
+        if (c < a.n) {
+          const double rf = (double)load_global(a.xref + c);
           const double d = (double)xv[j] - rf;
           e2 += d * d;
           r2s += rf * rf;
@@ -569,19 +501,13 @@ __device__ __forceinline__ void rt_run(DenseArgs<float> a, const int g, const in
   if (stop_code && tid == 0) set_status(a.status, stop_code);
   __builtin_amdgcn_s_waitcnt(0);  // no load of a step that will not run stays in flight
   __syncthreads();
-  if (h == 0)
-    for (int j = tid; j < wq * 4; j += kRtThreads) {
-      const int64_t c = c0 + j;
-      if (c < a.n) {
-        if constexpr (BATCH) {
-          store_global(a.x_star + c, xs[j]);
-          store_global(a.x + c, xv[j]);
-        } else {
-          a.x_star[c] = xs[j];
-          a.x[c] = xv[j];
-        }
-      }
+  for (int j = tid; j < wq * 4; j += kRtThreads) {
+    const int64_t c = c0 + j;
+    if (c < a.n) {
+      store_global(a.x_star + c, xs[j]);
+      store_global(a.x + c, xv[j]);
     }
+  }
   if (g == 0 && tid == 0) a.status[1] = (int)k_done;
 }
 

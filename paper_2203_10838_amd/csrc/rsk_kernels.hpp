@@ -100,10 +100,6 @@ __host__ __device__ inline int64_t onehop_lds_elems(int64_t G, int64_t eta) {
 // workgroup gathers all partials (one flat poll of at most 16 words per
 // thread of a 256-thread workgroup, then per-row sums in LDS).
 constexpr int64_t kOneHopWords = 4096;
-
-// The batched register tile gathers all C*eta partials in one hop only up to this many words per
-// step: above it the flat poll costs more than the two-hop exchange.
-constexpr int64_t kRtOneHopWords = 2048;
 // The single-system register tile: one hop up to this many words and one row a wave. Measured, us a
 // step, one hop / two hops: 32 workgroups, 16 rows 4.4 / 4.7, 24 rows 4.9 / 4.6, 64 rows 6.8 / 4.7; 63
 // workgroups, 16 rows 4.7 / 5.3; 128 workgroups, 8 rows 4.8 / 4.8, 16 rows 5.5 / 4.8; 256, 8 rows 5.5 / 5.2.
@@ -364,6 +360,12 @@ constexpr int kBrtPfBytes = 147456;
 constexpr int kBrtMaxEta = kBrtPasses * (kBrtThreads / 4);
 // default row bytes per workgroup per step of the register-tile launch (a tuned class overrides it)
 constexpr int64_t kBrtWgBytes = 256 * 1024;
+// Exchange in one hop (every workgroup reads every partial, a thread a row) up to this many words and a
+// row for each of the kBrtOneHopRows threads that do not issue the prefetch: 512 systems of up to
+// 8000 x 4000, 100 steps and the host's 2.9 ms: 18.9 ms with 2048, 18.4 with 4096 and with 8192, 19.8
+// with two hops above 32 rows.
+constexpr int64_t kBrtOneHopWords = 8192;
+constexpr int kBrtOneHopRows = kBrtThreads / 2;
 
 // Plan of one system on the batched register tile (the same function on host and device):
 // G_s from the row bytes per workgroup of the system's size class, at least enough slices for
@@ -383,13 +385,13 @@ __host__ __device__ inline bool batched_rt_plan(int64_t n, int eta, const BatchW
   if (G < gcpl) G = gcpl;
   if (G < 1) G = 1;
   const int own = kRtOwnMax * (kBrtThreads / 64);
-  if (G * eta > kRtOneHopWords || eta > own) {
+  if (G * eta > kBrtOneHopWords || eta > kBrtOneHopRows) {
     const int64_t gown = (eta + own - 1) / own;
     if (G < gown) G = gown;
   }
   if (G > gmax) return false;
   p->G = (int)G;
-  p->two_hop = (G * eta > kRtOneHopWords || eta > own) ? 1 : 0;
+  p->two_hop = (G * eta > kBrtOneHopWords || eta > kBrtOneHopRows) ? 1 : 0;
   p->tile_cache = 0;
   p->lds = 0;
   p->nchunks = nchunks;
