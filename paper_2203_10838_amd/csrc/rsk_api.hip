@@ -120,7 +120,8 @@ using rsk::kOneHopWords;
 // is faster (20000 columns, eta = 96 ... 256: 4-7% shorter steps)
 constexpr int kRtTwoGroupMinEta = 88, kRtTwoGroupMaxEta = 800;
 constexpr int kRtPfBytes = 147456;
-// (256 workgroups of 20000 columns, us a step without / with LO: eta = 16 7.4 / 6.9, 64 6.7 / 6.5, 96
+// (256 workgroups of 20000 columns, us a step without / with LO, 1 us less each since the column sums
+// read words: eta = 16 7.4 / 6.9, 64 6.7 / 6.5, 96
 // 7.2 / 7.2, 128 7.6 / 7.7)
 constexpr int kRtSmallEta = 95;
 // Ragged float32 rows (rows_ragged) take the one-workgroup kernel 4 wherever it applies, else the

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
   // LO: the steps whose length is a chain of latencies (many rows a wave, or few rows). A wave that
   // reduces several rows fetched their b and norms in branches, an index and a value round trip a
   // row: 3 us of a step of 64 rows. With LO lane j fetches row j of its wave, all rows at once, from
-  // indices loaded a step earlier (n = 500, eta = 64: 8.1 -> 4.5 us a step together with the second
+  // indices loaded a step earlier (n = 500, eta = 64: 8.1 -> 4.5 us a step, 3.5 with the column sums' words, together with the second
   // hop; eta = 256 5.1 -> 4.7; n = 20000, eta = 16 7.4 -> 6.9). Other steps hide the branch's wait
   // and keep it: n = 10000, eta = 256 7.2 us a step against 7.5 with LO.
   static_assert(!LO || (RG == 1 && kHbmSlots == 0), "lane-owned rows: one group, the whole next tile in LDS");
@@ -473,12 +473,10 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
     if (load_next && wave >= kPollWaves) load_tile();
     __syncthreads();  // publishes red[]
     if (tid < 4 * wq) {  // chunks past the slice carry clamped data: discarded
-      const int q = tid >> 2, e = tid & 3;
+      // one word a wave, all reads in flight (a chunk a wave and a select, one after another: 1 us more)
       float dsum = 0.f;
-      for (int w = 0; w < kRtWaves; ++w) {
-        const float4 v = red[w][q];
-        dsum += e == 0 ? v.x : e == 1 ? v.y : e == 2 ? v.z : v.w;
-      }
+#pragma unroll
+      for (int w = 0; w < kRtWaves; ++w) dsum += reinterpret_cast<const float*>(red[w])[tid];
       if constexpr (RG > 1) {
         // third hop: the slice's RG groups add their parts in group order, so every copy of the
         // slice gets the same x (the next step's HBM loads are in flight meanwhile)
