@@ -105,13 +105,20 @@ constexpr size_t kTileCacheBytes = 96 * 1024;
 constexpr size_t kPipeTileBytes = 128 * 1024;
 // General-kernel grid for grid = 0. A step is a chain of dependent round trips, so below a few MB
 // it is bound by latency, not bytes: one workgroup (no exchange) while the step and its rows are
-// small, else about 4 KB of rows per workgroup on 16..128 workgroups, the whole chip for big steps.
+// small, else about 4 KB of rows per workgroup on 16..128 workgroups, 192 from 3 MB, the whole chip for
+// big steps.
 constexpr size_t kOneWgStepBytes = 32 * 1024, kOneWgRowBytes = 16 * 1024;
 // the one-workgroup register kernel (kernel 4) is the float64 default for steps up to this size
 constexpr double kSmallStepBytes = 64.0 * 1024;
 constexpr size_t kBytesPerWg = 4 * 1024;
 constexpr int kMinSpreadG = 16, kMaxSpreadG = 128;
 constexpr size_t kFullGridStepBytes = size_t(8) << 20;
+// From this step size on the rows of 128 workgroups take longer than the exchange of more. Measured, float64,
+// us a step with 128 / 192 / 256: 5000 columns, 64 rows (2.6 MB) 10.2 / - / 10.4; 80 rows 12.7 / 10.6 / 10.7;
+// 128 rows 13.7 / 11.0 / 11.4; 6000 columns, 80 rows 12.7 / 10.5 / 11.0; 5000 columns, 200 rows (8 MB)
+// 20.1 / - / 14.4
+constexpr size_t kWideSpreadStepBytes = size_t(3) << 20;
+constexpr int kWideSpreadG = 192;
 using rsk::kOneHopWords;
 // the automatic choice takes two row groups of the register-tile kernel for eta in this range
 // (measured on 20000 columns: below it one group is as fast, the step being bound by the
@@ -328,6 +335,7 @@ int32_t plan_dense_fixed(const rsk_dense* A, const rsk_params* p, DensePlan* pl)
     } else {
       const double g = ceil(step_bytes / (double)kBytesPerWg);
       G = g < kMinSpreadG ? kMinSpreadG : g > kMaxSpreadG ? kMaxSpreadG : (int)g;
+      if (step_bytes >= kWideSpreadStepBytes) G = kWideSpreadG;
     }
     if (G >= 16) G -= G % 8;
   }
