@@ -543,9 +543,16 @@ int32_t plan_multirhs(const rsk_dense* A, int32_t R, const rsk_params* p, MultiP
   int S = pl->tile == 128 ? cus / tiles : (3 * cus + tiles - 1) / tiles;
   if (S >= 8 && pl->tile != 128) S = (S + 7) / 8 * 8;
   if (tuned && te.v0 >= 1) S = (int)(te.v0 < 4096 ? te.v0 : 4096);
-  // at least 256 columns a split by the built-in rule (128, four stages, for the wide tiles: 4096, 410,
-  // R = 128 31.5 us a step with 256, 29.6 with 128), at least 64 for a tuned split
-  const int64_t max_s = tuned && te.v0 >= 1 ? (A->n + 63) / 64 : pl->tile == 128 ? (A->n + 127) / 128 : most_s;
+  // at least 256 columns a split by the built-in rule, or 128 while the splits' tiles then fit one round on
+  // the CUs; at least 64 for a tuned split. Measured with 256 / 128: 4096, 410, R = 128, wide, 31.5 / 29.6 us
+  // a step; an unrolled step with its adjoint, 64 x 64, K = 20: 4096, 410, R = 64 2077 / 1978 us, 3000, 301, 16
+  // 1928 / 1714, 2000, 201, 32 1733 / 1560, 1000, 101, 64 1748 / 1485; more than a round: 4096, 410, 256, 64 x 64,
+  // 43.4 / 45.6 us a step
+  int64_t fit = cus / tiles;
+  if (fit >= 8 && pl->tile != 128) fit -= fit % 8;
+  int64_t max_s = (A->n + 127) / 128 < fit ? (A->n + 127) / 128 : fit;
+  if (max_s < most_s) max_s = most_s;
+  if (tuned && te.v0 >= 1) max_s = (A->n + 63) / 64;
   if (S > max_s) S = (int)max_s;
   if (S < 1) S = 1;
   pl->kspan = (A->n + S - 1) / S;
