@@ -470,8 +470,10 @@ int32_t rsk_plan_batched(int32_t nsys, int32_t dtype, const rsk_batch_item *item
  * through device-coherent stores and per-tile counters), 3 = the step kernels
  * with wide product tiles (128 x 128 for A_tau X, or 128 x 64 where those are too
  * few, for the fused update and whenever R <= 64; 512-thread workgroups; eta
- * padded to a multiple of 128; the float32 products formed from exact splits of
- * the operands into three bfloat16 pieces, six terms each, added in float32),
+ * padded to a multiple of 128; the float32 products formed from splits of the
+ * operands into three bfloat16 pieces, eight terms each, added in float32: what is
+ * left out is at most 2^-32 of a product, for operands of at least 2^-110 and
+ * products of at least 2^-102; smaller ones lose low bits, and an infinite operand gives NaN),
  * 0 = a tuned choice (rsk_tune_*), else 3 when eta >= 128 and either R > 64 or
  * eta * n >= 3900000, else 1.
  * Kernels 1 and 3 compute the same iteration with differently blocked sums

@@ -1,4 +1,5 @@
-// Multi-right-hand-side RSKA on the matrix cores (float32 MFMA, float32 accumulate).
+// Multi-right-hand-side RSKA on the matrix cores: float32 operands and accumulation, products on the
+// float32 cores (64 x 64 tiles) or, for the wide tiles, on the bfloat16 ones by pieces.
 //
 // R systems A X = B share A and the index stream. In the sketch-and-project
 // form of a step (eq. (rska1), start of Sec. 4) the R iterations together are
@@ -480,15 +481,22 @@ __global__ void init_multirhs(float* Xs, float* X, size_t total, float lambda, i
 // TN = 128, or 64), eight waves in a 4 x 2 grid, two a SIMD, so that one wave's products cover the
 // other's LDS reads and splitting.
 //
-// float32 operands on the bfloat16 matrix cores. Each operand element is split exactly into three
-// bfloat16 pieces, a = a1 + a2 + a3 (8 bits each: a1 truncates a, so it never overflows; a2 rounds
-// a - a1; a3 is what is left), and a product is the six terms a1 b3, a2 b2, a3 b1, a1 b2, a2 b1, a1 b1,
-// each an exact product added in float32. The three terms left out are below 2^-24 of the product
-// together, one rounding of the float32 matrix cores' own chain, which makes one a term where these
-// make one a stage (a1 b1 has accumulators of its own): the sums are closer to the exact ones (20 steps
-// of 32768 x 8192, R = 256, eta = 820: x* off by 1.3e-7 of its norm, 3.0e-7 on the float32 cores; n = 1280
-// ... 7000, R = 68 ... 256: 0.5 to 0.8 of the float32 cores' error). Six bfloat16 products take 3/8 of the
-// time of one in float32. Per launch at that size: A_tau X 33 us (44 in float32), the fused update 36 (44).
+// float32 operands on the bfloat16 matrix cores. Each operand element is split into three bfloat16
+// pieces, a = a1 + a2 + a3: a1 truncates a to 8 significant bits (so it never overflows), a2 rounds
+// a - a1, a3 is what is left; |a2| <= 2^-7 |a|, |a3| <= 2^-16 |a|. A product is the eight terms a2 b3,
+// a3 b2, a1 b3, a2 b2, a3 b1, a1 b2, a2 b1, a1 b1, each an exact product added in float32; a3 b3 alone is
+// left out, at most 2^-32 |a b|. (Without a2 b3 and a3 b2, up to 2^-22 |a b| together, a sum of one term
+// is off by up to four of its roundings.) a1 b1 has accumulators of its own: the seven other terms
+// are 2^-6 of the product, so their roundings do not count, and what is left is one rounding a stage of 32
+// terms and the last one, against one a term on the float32 matrix cores. Mean square error in units
+// of 2^-24 of the terms' sizes, float32 cores / these, normal operands, 1, 2, 4, 16, 128 terms: 0.426 / 0.426,
+// 0.50 / 0.48, 0.48 / 0.44, 0.37 / 0.28, 0.29 / 0.13; x* after 20 steps of 32768 x 8192, R = 256, eta = 820:
+// 3.0e-7 / 1.3e-7 of its norm.
+// Range: the split is exact for |a| >= 2^-110 and all its terms are normal numbers for |a b| >= 2^-102; terms
+// below 2^-126 are lost, so a sum below about 1e-29 in all loses bits that the float32 cores keep. An
+// infinite element gives NaN (a - a1).
+// Eight bfloat16 products take half of the time of one in float32. 32768 x 8192, R = 256, eta = 820: 78 us a
+// step (89 on the float32 cores, 70 with six terms).
 //
 // K advances 32 a stage. A thread loads 8 consecutive k of two columns (8 float2 loads, a wave one row's
 // 512 bytes; where k runs along memory, of two rows: 4 float4), splits them and writes the pieces as
@@ -560,7 +568,7 @@ __device__ __forceinline__ void put_pairs(u4v* tile, int oct, int col, const Pai
   put8<T>(tile, oct, tile_pos(col), f0);
   put8<T>(tile, oct, tile_pos(col + 1), f1);
 }
-// A wave's 16 x 16 blocks: a1 b1 in hi, the other terms in lo (2^-8 of it, so that their roundings do not
+// A wave's 16 x 16 blocks: a1 b1 in hi, the other terms in lo (2^-6 of it, so that their roundings do not
 // count)
 template <int TM, int TN>
 struct WideAcc {
@@ -588,14 +596,14 @@ __device__ __forceinline__ void mma_stage_w(const u4v* As, const u4v* Bs, int wm
     for (int j = 0; j < BJ; ++j)
       b[c][j] = __builtin_bit_cast(bf8, Bs[SplitTile<TN>::at(c, lk, wn * (TN / WGN) + j * 16 + li)]);
   }
-  constexpr int ta[6] = {0, 1, 2, 0, 1, 0}, tb[6] = {2, 1, 0, 1, 0, 0};
+  constexpr int ta[8] = {1, 2, 0, 1, 2, 0, 1, 0}, tb[8] = {2, 1, 2, 1, 0, 1, 0, 0};
 #pragma unroll
-  for (int q = 0; q < 6; ++q)
+  for (int q = 0; q < 8; ++q)
 #pragma unroll
     for (int i = 0; i < BI; ++i)
 #pragma unroll
       for (int j = 0; j < BJ; ++j) {
-        f4& d = q < 5 ? acc.lo[i][j] : acc.hi[i][j];
+        f4& d = q < 7 ? acc.lo[i][j] : acc.hi[i][j];
         d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[ta[q]][i], b[tb[q]][j], d, 0, 0, 0);
       }
 }

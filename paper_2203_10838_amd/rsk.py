@@ -314,7 +314,8 @@ def solve_multirhs(A: torch.Tensor, B: torch.Tensor, *, lam: float, eta: int, al
     """K RSKA steps for the R columns of B (m x R) at once; X*, X are n x R (row-major).
 
     ``kernel``: 1 the step kernels, 2 one persistent launch for all K steps, 3 the step kernels with
-    wide product tiles (float32 by exact bfloat16 pieces), 0 the library's choice (a tuned one, else 3 when
+    wide product tiles (float32 by three bfloat16 pieces, full precision for operands of at least
+    2^-110 and products of at least 2^-102), 0 the library's choice (a tuned one, else 3 when
     eta >= 128 and R > 64 or eta * n >= 3900000, else 1).
 
     With ``ckpt`` (ceil(K/ckpt_every) x n x R float32) the x* checkpoints the
