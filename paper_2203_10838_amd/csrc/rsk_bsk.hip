@@ -295,7 +295,9 @@ __global__ __launch_bounds__(kBskThreads) void bsk_lambda_max(const double* __re
       }
     const double pi = own ? beta * (p0 + p1) : 0.0;
     const double pv = lane_sum(pi * vi, 64);
-    const double wi = pi - 0.5 * beta * pv * vi;
+    // (no step where the column has nothing to eliminate or holds a NaN: a NaN row leaves the other rows'
+    // eigenvalue as it is, and the solve then reports the row)
+    const double wi = nx2 > 0.0 ? pi - 0.5 * beta * pv * vi : 0.0;
     ws[i] = wi;
     wave_lds_sync();
 #pragma unroll
