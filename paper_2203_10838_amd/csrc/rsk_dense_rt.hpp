@@ -21,7 +21,7 @@
 // 160 KB, of which HBM's share is 7 us. 512 systems of up to 8000 x 4000, 100 steps: 22.6 ms with the
 // indices fetched at the top of the step that needs them, the tile's bounds in vector registers (each
 // of its branches a mask), a prefetch loop that worked out each slot by itself (2.7 us where it had
-// next to nothing to load) and two hops for every system of more than 32 rows; 15.8 without these.
+// next to nothing to load) and two hops for every system of more than 32 rows; 15.0 without these.
 #pragma once
 #include "rsk_device.hpp"
 #include "rsk_kernels.hpp"
@@ -301,25 +301,32 @@ __device__ __forceinline__ void rt_run(const DenseArgs<float>& a, const int g, c
       __builtin_amdgcn_sched_barrier(0);
     }
     // b and ||a||^2 of the next step's owned rows and the indices of the step after it, under this
-    // step's exchange
+    // step's exchange: in one hop before its polls; in two, between the hops, since a wave's polls
+    // return after the loads it issued before them, and every workgroup waits for the owners' polls
+    // (40 systems of 8000 columns, 300 rows 123 -> 115 us a step; one hop gains nothing by it)
     float obn = 0.f, ornn = 1.f;
+    auto fetch_ahead = [&]() {
+      if (wave < kOwners) owned_inputs(oi, obn, ornn);
+      const int64_t k2 = k + 2 < a.K ? k + 2 : a.K - 1;
+      fetch_rows(k2);
+      oi = owned_index(k2);
+    };
     if (has_next) {
       // every wave has consumed its LDS slots (the dots used them): the next step's may land
       check_rows(rown, nerr);
       publish_rows(rown);
       __syncthreads();
       issue_prefetch();
-      if (wave < kOwners) owned_inputs(oi, obn, ornn);
-      const int64_t k2 = k + 2 < a.K ? k + 2 : a.K - 1;
-      fetch_rows(k2);
-      oi = owned_index(k2);
+      if (!a.two_hop) fetch_ahead();
     }
     int bad = 0;
     // reduce the owned rows over the slices; lane j: c_t = (alpha/eta)(r_t - b)/||a||^2 of row j
     float osum = 0.f;
     if (!a.two_hop) {
       if (omine) {
-        constexpr int kN = 8;
+        // four slices a round trip: eight take 16 registers more, and what the two-hop form then spills
+        // waits behind the prefetch when it is loaded again (the 40 systems 115 -> 103 us a step)
+        constexpr int kN = 4;
         for (int s0 = 0; s0 < G; s0 += kN) {
           float v[kN];
           wait_tagged_batch(&xP[(size_t)s0 * eta + orow], (size_t)eta, G - s0 < kN ? G - s0 : kN, tag, v, lerr);
@@ -364,6 +371,7 @@ __device__ __forceinline__ void rt_run(const DenseArgs<float>& a, const int g, c
         bad |= !isfinite(c);
       }
     }
+    if (has_next && a.two_hop) fetch_ahead();
     ob = obn;
     orn = ornn;
     if (a.two_hop && tid < kRtRowsPerPass) {

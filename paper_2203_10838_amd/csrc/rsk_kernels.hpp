@@ -360,12 +360,18 @@ constexpr int kBrtPfBytes = 147456;
 constexpr int kBrtMaxEta = kBrtPasses * (kBrtThreads / 4);
 // default row bytes per workgroup per step of the register-tile launch (a tuned class overrides it)
 constexpr int64_t kBrtWgBytes = 256 * 1024;
-// Exchange in one hop (every workgroup reads every partial, a thread a row) up to this many words and a
-// row for each of the kBrtOneHopRows threads that do not issue the prefetch: 512 systems of up to
-// 8000 x 4000, 100 steps and the host's 2.9 ms: 18.9 ms with 2048, 18.4 with 4096 and with 8192, 19.8
-// with two hops above 32 rows.
-constexpr int64_t kBrtOneHopWords = 8192;
+// Exchange in one hop (every workgroup reads every partial, a thread a row, four slices a round trip) for
+// few enough slices, as a thread's round trips grow with them, and a row for each of the kBrtOneHopRows
+// threads that do not issue the prefetch. Measured, us a step, one hop / two, by workgroups G and rows, slices
+// of 64 columns: G = 2, 2 rows 8.1 / 9.1, 64 8.2 / 11.5; G = 8, 2 8.4 / 9.3, 64 9.0 / 9.9, 256 10.4 / 12.3; G = 13,
+// 2 8.7 / 8.8, 64 9.4 / 9.2, 256 10.8 / 11.0; G = 16, 32 9.0 / 8.5, 128 9.3 / 9.1, 200 10.2 / 10.5; G = 24, 2 8.2 /
+// 7.5, 64 9.1 / 8.1, 200 10.5 / 9.5; G = 64, 64 13.2 / 7.0; G = 256, 32 36 / 7.1. 512 systems of up to
+// 8000 x 4000, 100 steps and the host's 2.9 ms: 17.7 ms with one hop up to 16, 18.0 up to 8, 18.8 for 1 alone.
+constexpr int kBrtOneHopG = 16;
 constexpr int kBrtOneHopRows = kBrtThreads / 2;
+__host__ __device__ inline bool batched_rt_two_hop(int64_t G, int eta) {
+  return G > kBrtOneHopG || eta > kBrtOneHopRows;
+}
 
 // Plan of one system on the batched register tile (the same function on host and device):
 // G_s from the row bytes per workgroup of the system's size class, at least enough slices for
@@ -385,13 +391,13 @@ __host__ __device__ inline bool batched_rt_plan(int64_t n, int eta, const BatchW
   if (G < gcpl) G = gcpl;
   if (G < 1) G = 1;
   const int own = kRtOwnMax * (kBrtThreads / 64);
-  if (G * eta > kBrtOneHopWords || eta > kBrtOneHopRows) {
+  if (batched_rt_two_hop(G, eta)) {
     const int64_t gown = (eta + own - 1) / own;
     if (G < gown) G = gown;
   }
   if (G > gmax) return false;
   p->G = (int)G;
-  p->two_hop = (G * eta > kBrtOneHopWords || eta > kBrtOneHopRows) ? 1 : 0;
+  p->two_hop = batched_rt_two_hop(G, eta) ? 1 : 0;
   p->tile_cache = 0;
   p->lds = 0;
   p->nchunks = nchunks;
