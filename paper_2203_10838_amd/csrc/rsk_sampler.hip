@@ -42,6 +42,33 @@ __device__ __forceinline__ void philox4x32_10(uint32_t (&c)[4], uint32_t k0, uin
 
 }  // namespace
 
+// One draw: the target of step k0 + e / eta, slot e % eta.
+__device__ __forceinline__ double draw_target(int64_t e, int eta, int64_t k0, uint32_t key0, uint32_t key1, double total) {
+  const int64_t k = k0 + e / eta;
+  uint32_t c[4] = {(uint32_t)(e % eta), (uint32_t)k, (uint32_t)((uint64_t)k >> 32), 0u};
+  philox4x32_10(c, key0, key1);
+  const uint64_t bits = ((uint64_t)(c[0] >> 5) << 26) | (uint64_t)(c[1] >> 6);
+  return (double)bits * (1.0 / 9007199254740992.0) * total;
+}
+
+// A draw a thread, every level of its binary search read from the cdf.
+__global__ __launch_bounds__(256) void sample_direct_kernel(const double* __restrict__ cdf, int64_t m, uint32_t key0,
+                                                            uint32_t key1, int64_t k0, int64_t K, int eta,
+                                                            int32_t* __restrict__ out) {
+  const double total = cdf[m - 1];
+  const int64_t N = K * (int64_t)eta;
+  for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < N; e += (int64_t)gridDim.x * blockDim.x) {
+    const double target = draw_target(e, eta, k0, key0, key1, total);
+    int64_t lo = 0, hi = m;
+    while (lo < hi) {
+      const int64_t mid = lo + ((hi - lo) >> 1);
+      if (cdf[mid] > target) hi = mid;
+      else lo = mid + 1;
+    }
+    out[e] = (int32_t)(lo < m ? lo : m - 1);
+  }
+}
+
 // Binary search in two levels. kPivots evenly spaced cdf values sit in LDS: the first levels of
 // the search read those, and only the last log2(m / kPivots) (a stretch of a few cache lines) read
 // the cdf itself; kIlp searches a thread run side by side, so one's loads are in flight under the
@@ -50,6 +77,13 @@ __device__ __forceinline__ void philox4x32_10(uint32_t (&c)[4], uint32_t k0, uin
 // draws from 100000 rows in 213 us (320 us with every level read from the cdf).
 constexpr int kPivots = 4096, kSampleThreads = 1024, kIlp = 4;
 constexpr int64_t kSampleBlocks = 512;
+// Every workgroup fills its pivots from as many cache lines of the cdf, and a long stretch leaves most of a
+// search outside them, so the two levels pay for many draws from a cdf of middle length. Measured, us, one
+// level / two: 64 draws from 1000, 100000, 10^7 rows 13 / 16, 13 / 20, 13 / 67; 2^18 draws from 100000
+// 16 / 23; 2^20 draws from 1000, 8192, 100000, 10^6, 2 10^6, 10^7 17 / 16, 30 / 19, 51 / 38, 76 / 70,
+// 100 / 109, 158 / 191; 2^23 draws from 64, 1000, 100000, 10^6, 2 10^6 62 / 60, 84 / 67, 337 / 193, 526 / 444,
+// 697 / 771.
+constexpr int64_t kTwoLevelDraws = 1 << 20, kTwoLevelMinM = 1000, kTwoLevelMaxM = 1 << 20;
 
 __global__ __launch_bounds__(kSampleThreads) void sample_stream_kernel(const double* __restrict__ cdf, int64_t m,
                                                                        uint32_t key0, uint32_t key1, int64_t k0,
@@ -72,12 +106,7 @@ __global__ __launch_bounds__(kSampleThreads) void sample_stream_kernel(const dou
     int lo[kIlp], hi[kIlp];
 #pragma unroll
     for (int u = 0; u < kIlp; ++u) {
-      const int64_t e = base + u * kSampleThreads + threadIdx.x;
-      const int64_t k = k0 + e / eta;
-      uint32_t c[4] = {(uint32_t)(e % eta), (uint32_t)k, (uint32_t)((uint64_t)k >> 32), 0u};
-      philox4x32_10(c, key0, key1);
-      const uint64_t bits = ((uint64_t)(c[0] >> 5) << 26) | (uint64_t)(c[1] >> 6);
-      target[u] = (double)bits * (1.0 / 9007199254740992.0) * total;
+      target[u] = draw_target(base + u * kSampleThreads + threadIdx.x, eta, k0, key0, key1, total);
       lo[u] = 0;
       hi[u] = np;
     }
@@ -227,6 +256,13 @@ hipError_t launch_sample_stream(const double* cdf, int64_t m, uint64_t seed, int
                                 int32_t* out, hipStream_t stream) {
   const int64_t N = K * (int64_t)eta;
   if (N == 0) return hipSuccess;
+  if (N < kTwoLevelDraws || m < kTwoLevelMinM || m > kTwoLevelMaxM) {
+    int64_t blocks = (N + 255) / 256;
+    if (blocks > 65536) blocks = 65536;
+    hipLaunchKernelGGL(sample_direct_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, cdf, m, (uint32_t)seed,
+                       (uint32_t)(seed >> 32), k0, K, eta, out);
+    return hipGetLastError();
+  }
   // two 1024-thread workgroups a CU at most, so that each fills its pivots once for many searches
   int64_t blocks = (N + kSampleThreads * kIlp - 1) / (kSampleThreads * kIlp);
   if (blocks > kSampleBlocks) blocks = kSampleBlocks;
