@@ -131,6 +131,8 @@ constexpr int kRtPfBytes = 147456;
 // read words: eta = 16 7.4 / 6.9, 64 6.7 / 6.5, 96
 // 7.2 / 7.2, 128 7.6 / 7.7)
 constexpr int kRtSmallEta = 95;
+// largest eta of the 1024-thread form
+constexpr int kRtWideEta = 768;
 // Ragged float32 rows (rows_ragged) take the one-workgroup kernel 4 wherever it applies, else the
 // register tile from this length on (its slices then span more than one workgroup), else the
 // general kernel. Measured, us a step, general kernel / register tile / kernel 4: n = 65, eta = 1
@@ -226,11 +228,14 @@ bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* p
     G = (int)(nunits * rg);
     // fewer units than workgroups: a power of two of them (the owners' polls are then whole waves and
     // the slices whole XCD rounds). Measured, us a step, nunits / the power of two below: 63 / 32
-    // workgroups, eta = 64 5.7 / 4.8, eta = 16 4.8 / 4.9; 94 / 64, eta = 334 6.7 / 6.2; 209 / 128, eta = 16
-    // 5.4 / 4.8, eta = 334 7.9 / 6.5, eta = 1000 10.3 / 9.9; below 32 the units themselves: 19 / 16,
-    // eta = 150 4.6 / 5.1
-    // (fewer than 16 rows: the units too; 63 / 32, eta = 1 4.1 / 4.6, eta = 8 4.5 / 4.7)
-    if (p->grid <= 0 && rg == 1 && G >= 32 && p->eta >= 16)
+    // workgroups, eta = 64 5.0 / 4.1, 128 5.0 / 4.7, 512 6.2 / 6.4; 94 / 64, eta = 64 5.0 / 4.2, 256 5.3 / 5.2;
+    // 127 / 64, eta = 64 5.4 / 4.2, 334 6.4 / 5.9, 768 8.6 / 7.8; 209 / 128, eta = 16 4.8 / 4.1, 334 6.9 / 6.4,
+    // 768 9.0 / 8.2; 255 / 128, eta = 64 5.7 / 4.2, 768 10.6 / 8.3. The 512-thread form (eta > 768) holds twice
+    // the rows a lane, and slices twice as wide cost it more than the exchange: eta = 1024, 48 / 32 9.3 / 12.5, 63 /
+    // 32 8.8 / 12.2, 94 / 64 8.7 / 10.5, 127 / 64 8.9 / 10.3, 209 / 128 8.4 / 9.5 (255 / 128 10.7 / 9.6): the
+    // units themselves there; below 32 units too (19 / 16, eta = 150 4.6 / 5.1), and for fewer than 16 rows (63 / 32,
+    // eta = 1 4.1 / 4.6, eta = 8 4.5 / 4.7)
+    if (p->grid <= 0 && rg == 1 && G >= 32 && p->eta >= 16 && p->eta <= kRtWideEta)
       while (G & (G - 1)) G &= G - 1;
   }
   if (rg > 1 && G >= 16) G -= G % 8;  // whole XCD rounds keep a slice's groups on one XCD
@@ -241,7 +246,7 @@ bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* p
   const int64_t upm = (nunits + C - 1) / C;  // units of the widest slice
   const int cpl = (int)((upm + rg - 1) / rg);
   if (cpl > rsk::kRtMaxCPL || p->eta > rsk::kRtMaxEta) return false;
-  const int nt = p->eta <= 768 ? 1024 : 512;
+  const int nt = p->eta <= kRtWideEta ? 1024 : 512;
   const int etaR = (p->eta + rg - 1) / rg;
   const int rpp = nt / (4 * rg);  // group rows of one pass
   const int rp = (etaR + rpp - 1) / rpp;
