@@ -105,18 +105,22 @@ constexpr size_t kTileCacheBytes = 96 * 1024;
 constexpr size_t kPipeTileBytes = 128 * 1024;
 // General-kernel grid for grid = 0. A step is a chain of dependent round trips, so below a few MB
 // it is bound by latency, not bytes: one workgroup (no exchange) while the step and its rows are
-// small, else about 4 KB of rows per workgroup on 16..128 workgroups, 192 from 3 MB, the whole chip for
-// big steps.
+// small, else about 4 KB of rows per workgroup on 16..128 workgroups (192 for some steps from 3 MB), the whole
+// chip for big steps.
 constexpr size_t kOneWgStepBytes = 32 * 1024, kOneWgRowBytes = 16 * 1024;
 // the one-workgroup register kernel (kernel 4) is the float64 default for steps up to this size
 constexpr double kSmallStepBytes = 64.0 * 1024;
 constexpr size_t kBytesPerWg = 4 * 1024;
 constexpr int kMinSpreadG = 16, kMaxSpreadG = 128;
 constexpr size_t kFullGridStepBytes = size_t(8) << 20;
-// From this step size on the rows of 128 workgroups take longer than the exchange of more. Measured, float64,
-// us a step with 128 / 192 / 256: 5000 columns, 64 rows (2.6 MB) 10.2 / - / 10.4; 80 rows 12.7 / 10.6 / 10.7;
-// 128 rows 13.7 / 11.0 / 11.4; 6000 columns, 80 rows 12.7 / 10.5 / 11.0; 5000 columns, 200 rows (8 MB)
-// 20.1 / - / 14.4
+// From this step size on the rows of 128 workgroups take longer than the exchange of 192, where 192 halve the
+// lanes that share a row (a power of two, at least the widest slice's chunks): twice the rows in flight. Where
+// they do not, the larger exchange is all that changes. Measured, us a step with 128 / 192, float64: n = 700
+// (4 -> 2 lanes), 4 MB 18.2 / 15.9; 1500 (8 -> 4), 3 MB 13.9 / 12.6, 8 MB 21.7 / 17.7; 3000 (16 -> 8), 4 MB
+// 13.8 / 11.0; 5000 (32 -> 16), 3 MB 12.5 / 10.5, 8 MB 19.7 / 15.0; the lanes as before: n = 500 3 MB 16.4 /
+// 18.5, 1000 3 MB 12.4 / 14.3, 6 MB 18.7 / 20.8, 2000 4 MB 14.7 / 14.8, 8000 3 MB 10.1 / 10.6, 16000 4 MB 10.4 /
+// 10.8; fewer than two chunks a slice: n = 350 3 MB 20.2 / 21.3, 8 MB 40.1 / 44.1. float32, n = 1500 (4 -> 2), eta =
+// 1100 21.1 / 19.2; 1000 (2, 2) 18.4 / 19.3.
 constexpr size_t kWideSpreadStepBytes = size_t(3) << 20;
 constexpr int kWideSpreadG = 192;
 using rsk::kOneHopWords;
@@ -340,7 +344,10 @@ int32_t plan_dense_fixed(const rsk_dense* A, const rsk_params* p, DensePlan* pl)
     } else {
       const double g = ceil(step_bytes / (double)kBytesPerWg);
       G = g < kMinSpreadG ? kMinSpreadG : g > kMaxSpreadG ? kMaxSpreadG : (int)g;
-      if (step_bytes >= kWideSpreadStepBytes) G = kWideSpreadG;
+      if (step_bytes >= kWideSpreadStepBytes) {
+        const auto lanes = [&](int wgs) { return next_pow2((int)((pl->nchunks + wgs - 1) / wgs)); };
+        if (lanes(kWideSpreadG) > 1 && lanes(kWideSpreadG) < lanes(kMaxSpreadG)) G = kWideSpreadG;
+      }
     }
     if (G >= 16) G -= G % 8;
   }
