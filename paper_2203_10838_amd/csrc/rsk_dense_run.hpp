@@ -604,37 +604,52 @@ __device__ __forceinline__ void dense_run(const DenseArgs<T>& a, const int g, co
         red[rg * wq + q] = acc;
       }
       __syncthreads();
-      // P lanes a chunk (one wave for few chunks), each every P-th part, eight at a time in flight: one
-      // lane adding its parts one after another took 2.2 us a step where a slice had few chunks (n = 1000,
-      // eta = 100, float64, 128 workgroups: 11.3 -> 9.1 us a step with the polls above)
-      int P = 1;
-      while (2 * P * wq <= 64 && nrg > 8 * P) P *= 2;
-      const int q = tid / P, r0 = tid % P;
-      if (q < wq) {
-        V d;
+      auto apply = [&](int q, const V& d) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) d.v[e] = T(0);
-        for (int r = r0; r < nrg; r += 8 * P) {
-          V o[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) o[u] = red[(r + u * P < nrg ? r + u * P : r) * wq + q];
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-            if (r + u * P < nrg) {
-#pragma unroll
-              for (int e = 0; e < VEC; ++e) d.v[e] += o[u].v[e];
-            }
+        for (int e = 0; e < VEC; ++e) {
+          const int j = q * VEC + e;
+          const T z = xs[j] - d.v[e];
+          xs[j] = z;
+          xv[j] = shrink(z, a.lambda);
         }
+      };
+      if (nrg <= 8) {
+        // few parts: one after another by the chunk's thread (40 systems of 300 columns, one row a step, in
+        // a batch: 12.3 us a step, 13.0 in the form below)
+        if (tid < wq) {
+          V d = red[tid];
+          for (int r = 1; r < nrg; ++r) {
+            const V o = red[r * wq + tid];
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) d.v[e] = lane_sum(d.v[e], P);
-        if (r0 == 0) {
-#pragma unroll
-          for (int e = 0; e < VEC; ++e) {
-            const int j = q * VEC + e;
-            const T z = xs[j] - d.v[e];
-            xs[j] = z;
-            xv[j] = shrink(z, a.lambda);
+            for (int e = 0; e < VEC; ++e) d.v[e] += o.v[e];
           }
+          apply(tid, d);
+        }
+      } else {
+        // P lanes a chunk (one wave for few chunks), each every P-th part, eight at a time in flight: one
+        // lane adding its parts one after another took 2.2 us a step where a slice had few chunks (n = 1000,
+        // eta = 100, float64, 128 workgroups: 11.3 -> 9.1 us a step with the polls above)
+        int P = 1;
+        while (2 * P * wq <= 64 && nrg > 8 * P) P *= 2;
+        const int q = tid / P, r0 = tid % P;
+        if (q < wq) {
+          V d;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) d.v[e] = T(0);
+          for (int r = r0; r < nrg; r += 8 * P) {
+            V o[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o[u] = red[(r + u * P < nrg ? r + u * P : r) * wq + q];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+              if (r + u * P < nrg) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) d.v[e] += o[u].v[e];
+              }
+          }
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) d.v[e] = lane_sum(d.v[e], P);
+          if (r0 == 0) apply(q, d);
         }
       }
     } else {
