@@ -441,6 +441,7 @@ int32_t check_csr(const rsk_csr* A) {
 // exponent words and the monitor words.
 struct CsrPlan {
   int kernel, G;
+  bool one;  // the grid kernel with one pass of rows (csr_one_pass)
   size_t offYcnt, offCy, offBar, offEmax, offM, offAcc2, bytes;
 };
 
@@ -452,6 +453,7 @@ int32_t plan_csr(const rsk_csr* A, const rsk_params* p, CsrPlan* pl) {
   const bool grid = p->kernel == 2 || (p->kernel == 0 && p->eta >= 4);
   pl->kernel = grid ? 2 : 1;
   pl->G = 1;
+  pl->one = false;
   size_t o = align256((size_t)(A->n + 1) * sizeof(long long));
   pl->offYcnt = pl->offCy = 0;
   if (p->y_out) {
@@ -468,11 +470,11 @@ int32_t plan_csr(const rsk_csr* A, const rsk_params* p, CsrPlan* pl) {
     pl->G = G;
     // one pass: two exchange words a workgroup; else a global barrier counter and 8 group counters, 128
     // bytes apart
-    const bool one = rsk::csr_one_pass(p->eta, G);
-    pl->offBar = o; o += one ? 2 * rsk::kCsrRowsMaxG * sizeof(u64) : 9 * 128;
+    pl->one = rsk::csr_one_pass(p->eta, G, rsk::csr_rows_max_resident<T>());
+    pl->offBar = o; o += pl->one ? 2 * rsk::kCsrRowsMaxG * sizeof(u64) : 9 * 128;
     pl->offEmax = o; o += 64;
     pl->offM = o; o = align256(o + (size_t)G * 4 * sizeof(u64));
-    if (one) { pl->offAcc2 = o; o += align256((size_t)(A->n + 1) * sizeof(long long)); }
+    if (pl->one) { pl->offAcc2 = o; o += align256((size_t)(A->n + 1) * sizeof(long long)); }
   }
   pl->bytes = o;
   return RSK_OK;
@@ -506,7 +508,7 @@ int32_t solve_csr_t(const rsk_csr* A, const void* b, const rsk_params* p, void* 
   a.xM = (u64*)(w + pl.offM);
   if (rsk::launch_zero_words((u64*)ws, pl.bytes / sizeof(u64), stream) != hipSuccess) return RSK_ERR_HIP;
   if (rsk::launch_zero_status(p->status_dev, stream) != hipSuccess) return RSK_ERR_HIP;
-  const hipError_t e = pl.kernel == 2 ? rsk::launch_csr_grid<T>(a, stream) : rsk::launch_csr<T>(a, stream);
+  const hipError_t e = pl.kernel == 2 ? rsk::launch_csr_grid<T>(a, pl.one, stream) : rsk::launch_csr<T>(a, stream);
   return e == hipSuccess ? RSK_OK : RSK_ERR_HIP;
 }
 

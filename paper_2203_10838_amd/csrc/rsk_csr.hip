@@ -878,34 +878,33 @@ __global__ __launch_bounds__(kRowsThreads) void rska_csr_rows(CsrArgs<T> a) {
   if (g == 0 && tid == 0) a.status[1] = (int)k_done;
 }
 
-template <typename T>
-int csr_grid_max_resident() {
+static int max_resident(const void* fn, int threads) {
   int per_cu = 0;
-  int one = 0;  // of either kernel
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)&rska_csr_grid<T>, kGridThreads, 0) !=
-          hipSuccess ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&one, (const void*)&rska_csr_rows<T>, kRowsThreads, 0) !=
-          hipSuccess)
-    return 0;
-  if (one < 1) return 0;  // (its grids are at most one workgroup a CU)
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, 0) != hipSuccess) return 0;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess) return 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
   return per_cu * cus;
 }
+template <typename T>
+int csr_grid_max_resident() { return max_resident((const void*)&rska_csr_grid<T>, kGridThreads); }
+template <typename T>
+int csr_rows_max_resident() { return max_resident((const void*)&rska_csr_rows<T>, kRowsThreads); }
 
 template <typename T>
-hipError_t launch_csr_grid(CsrArgs<T>& a, hipStream_t stream) {
-  if (a.G < 1 || a.G > csr_grid_max_resident<T>()) return hipErrorCooperativeLaunchTooLarge;
+hipError_t launch_csr_grid(CsrArgs<T>& a, bool one, hipStream_t stream) {
+  if (a.G < 1 || a.G > (one ? csr_rows_max_resident<T>() : csr_grid_max_resident<T>()))
+    return hipErrorCooperativeLaunchTooLarge;
   void* args[] = {&a};
-  if (csr_one_pass(a.eta, a.G))
-    return launch_persistent((const void*)&rska_csr_rows<T>, dim3(a.G), dim3(kRowsThreads), args, 0, stream);
+  if (one) return launch_persistent((const void*)&rska_csr_rows<T>, dim3(a.G), dim3(kRowsThreads), args, 0, stream);
   return launch_persistent((const void*)&rska_csr_grid<T>, dim3(a.G), dim3(kGridThreads), args, 0, stream);
 }
 
 template int csr_grid_max_resident<float>();
 template int csr_grid_max_resident<double>();
-template hipError_t launch_csr_grid<float>(CsrArgs<float>&, hipStream_t);
-template hipError_t launch_csr_grid<double>(CsrArgs<double>&, hipStream_t);
+template int csr_rows_max_resident<float>();
+template int csr_rows_max_resident<double>();
+template hipError_t launch_csr_grid<float>(CsrArgs<float>&, bool, hipStream_t);
+template hipError_t launch_csr_grid<double>(CsrArgs<double>&, bool, hipStream_t);
 
 }  // namespace rsk

@@ -144,16 +144,23 @@ struct CsrArgs {
 template <typename T>
 hipError_t launch_csr(CsrArgs<T>& a, hipStream_t stream);
 // Multi-workgroup CSR kernels (one lane per nonzero): where every workgroup holds its 8 rows of a
-// step in one pass and G <= kCsrRowsMaxG, the one with two exchanges a step (rska_csr_rows), else
-// the one with three grid barriers (rska_csr_grid).
+// step in one pass, G <= kCsrRowsMaxG and the device holds G of its workgroups at once, the one with two
+// exchanges a step (rska_csr_rows), else the one with three grid barriers (rska_csr_grid).
 constexpr int kCsrRowsMaxG = 256;
 constexpr int kCsrGridRowsPerPass = 8;   // rows per workgroup and pass (256 threads, 32 lanes a row)
 constexpr int kCsrGridMaxPasses = 8;
-inline bool csr_one_pass(int eta, int G) { return G <= kCsrRowsMaxG && eta <= kCsrGridRowsPerPass * G; }
+// resident: workgroups of rska_csr_rows the device holds (0: not known)
+inline bool csr_one_pass(int eta, int G, int resident) {
+  return G <= kCsrRowsMaxG && eta <= kCsrGridRowsPerPass * G && (resident == 0 || G <= resident);
+}
+// Workgroups of rska_csr_grid and of rska_csr_rows the current device holds at once (0: the query failed).
 template <typename T>
 int csr_grid_max_resident();
 template <typename T>
-hipError_t launch_csr_grid(CsrArgs<T>& a, hipStream_t stream);
+int csr_rows_max_resident();
+// one: csr_one_pass of the plan
+template <typename T>
+hipError_t launch_csr_grid(CsrArgs<T>& a, bool one, hipStream_t stream);
 
 // Multi-RHS (shared A and stream), float32 MFMA GEMMs per step.
 struct MultiRhsArgs {
