@@ -238,7 +238,10 @@ int32_t rsk_bsk_solve_dense(const rsk_dense *A, const void *b, const rsk_params 
  * launches the library supports: results are those of the explicit choice,
  * bit for bit, and a tuned choice that does not apply to a matrix (alignment,
  * leading dimension) falls back to the built-in rule.
- *   path RSK_TUNE_DENSE:    key (dtype, m, n, eta);    v0 = kernel (1..4), v1 = grid.
+ *   path RSK_TUNE_DENSE:    key (dtype, m, n, eta, R); v0 = kernel (1..4), v1 = grid (v0 = 0: the built-in
+ *                           rules). R = 1: float32 rows that are not whole 16-byte chunks (see
+ *                           rsk_avg_solve_dense), which look for it first; R = 0: all others,
+ *                           and those rows where they have no entry.
  *   path RSK_TUNE_MULTIRHS: key (dtype, m, n, eta, R); v0 = S (splits of the n columns in
  *                           A_tau X), v1 = S2 (row splits of A_tau^T C: 1, 2, 4 or 8), v2 = the
  *                           kernel (1 step kernels, 2 one persistent launch, 3 wide-tile step

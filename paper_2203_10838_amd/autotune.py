@@ -5,7 +5,7 @@ batched per-system workgroup targets with wg_bytes = 0). ``save``/``load`` keep 
 text cache file; the library also loads the file named by RSK_TUNE_CACHE at its first lookup.
 
 What is tuned, per key:
-* dense (dtype, m, n, eta): the kernel (general; register tile with one or two row groups; one
+* dense (dtype, m, n, eta, and R = 1 for float32 rows that are not whole 16-byte chunks): the kernel (general; register tile with one or two row groups; one
   workgroup with the step in registers) and its workgroup count, among the launches rsk_plan_dense
   accepts;
 * multi-RHS (dtype, m, n, eta, R): S, the column splits of A_tau X, and S2, the row splits of
@@ -108,13 +108,23 @@ def dense_candidates(A: torch.Tensor, eta: int) -> list:
     return out
 
 
+def dense_ragged(A: torch.Tensor) -> bool:
+    """Float32 rows that are not whole 16-byte chunks on 16-byte boundaries: their launches, and so their tuned
+    entries (key R = 1), are others than those of aligned rows of the same shape."""
+    return A.dtype == torch.float32 and (A.shape[1] % 4 != 0 or A.stride(0) % 4 != 0 or A.data_ptr() % 16 != 0)
+
+
 def tune_dense(A: torch.Tensor, b: torch.Tensor, *, eta: int, lam: float, alpha: float, index_stream: torch.Tensor,
                steps: int = 20, reps: int = 3, candidates: Optional[Iterable] = None, install: bool = True,
                rownorm2_t: Optional[torch.Tensor] = None) -> dict:
     """Time every (kernel, grid) candidate on ``steps`` steps of the given stream; install the fastest
-    for (dtype, m, n, eta). Returns {"choice": (kernel, grid), "us_per_step", "default", "table"}."""
+    for (dtype, m, n, eta), or no choice of a kernel ((0, 0)) where the built-in launch is not among them and beats
+    them: with the default candidates, and on ragged rows, whose register tile is the library's choice only, with
+    any. Returns {"choice": (kernel, grid), "us_per_step", "default", "table"}."""
     m, n = A.shape
     dtype = rsk._dtype_code(A)
+    ragged = dense_ragged(A)
+    key = dict(m=m, n=n, eta=eta, R=1 if ragged else 0)
     r2 = rownorm2_t if rownorm2_t is not None else rsk.rownorm2(A)
     cands = list(candidates) if candidates is not None else dense_candidates(A, eta)
     x_star = torch.empty(n, dtype=A.dtype, device=A.device)
@@ -123,8 +133,15 @@ def tune_dense(A: torch.Tensor, b: torch.Tensor, *, eta: int, lam: float, alpha:
         return rsk.solve_dense(A, b, lam=lam, eta=eta, alpha=alpha, K=steps, index_stream=index_stream,
                                rownorm2_t=r2, kernel=kernel, grid=grid, x_star=x_star, check=False)
 
-    prev = get_entry(_abi.RSK_TUNE_DENSE, dtype, m=m, n=n, eta=eta)
-    erase(_abi.RSK_TUNE_DENSE, dtype, m=m, n=n, eta=eta)   # the built-in choice, timed without an entry
+    def built_in():
+        # an entry of ragged rows that names no kernel keeps them from the shape's other entry
+        if ragged:
+            set_entry(_abi.RSK_TUNE_DENSE, dtype, v0=0, **key)
+        else:
+            erase(_abi.RSK_TUNE_DENSE, dtype, **key)
+
+    prev = get_entry(_abi.RSK_TUNE_DENSE, dtype, **key)
+    built_in()   # the built-in choice, timed without an entry
     default_plan = rsk.plan_dense(A, eta=eta)
     default_ms = _time_ms(lambda: run(0, 0), reps)
     table = []
@@ -132,19 +149,16 @@ def tune_dense(A: torch.Tensor, b: torch.Tensor, *, eta: int, lam: float, alpha:
         ms = _time_ms(lambda: run(kernel, grid), reps)
         table.append({"kernel": kernel, "grid": grid, "us_per_step": ms * 1e3 / steps})
     best = min(table, key=lambda r: r["us_per_step"])
-    # the built-in launch is not always among the candidates (the register tile on unaligned rows is
-    # the library's choice only): no entry then, if none of them beats it
-    builtin = (candidates is None and (default_plan["kernel"], default_plan["G"]) not in cands
-               and default_ms * 1e3 / steps < best["us_per_step"])
-    if install and builtin:
-        pass
-    elif install:
-        set_entry(_abi.RSK_TUNE_DENSE, dtype, m=m, n=n, eta=eta, v0=best["kernel"], v1=best["grid"],
-                  us=best["us_per_step"])
-    elif prev is not None:
-        set_entry(_abi.RSK_TUNE_DENSE, dtype, m=m, n=n, eta=eta, v0=prev["v0"], v1=prev["v1"], us=prev["us"])
-    if builtin:
+    if ((candidates is None or ragged) and (default_plan["kernel"], default_plan["G"]) not in cands
+            and default_ms * 1e3 / steps < best["us_per_step"]):
         best = {"kernel": 0, "grid": 0, "us_per_step": default_ms * 1e3 / steps}
+    if install:
+        if best["kernel"]:
+            set_entry(_abi.RSK_TUNE_DENSE, dtype, v0=best["kernel"], v1=best["grid"], us=best["us_per_step"], **key)
+    elif prev is not None:
+        set_entry(_abi.RSK_TUNE_DENSE, dtype, v0=prev["v0"], v1=prev["v1"], us=prev["us"], **key)
+    else:
+        erase(_abi.RSK_TUNE_DENSE, dtype, **key)
     return {"choice": (best["kernel"], best["grid"]), "us_per_step": best["us_per_step"],
             "default": {"plan": default_plan, "us_per_step": default_ms * 1e3 / steps}, "table": table}
 

@@ -281,13 +281,16 @@ template <typename T>
 int32_t plan_dense_fixed(const rsk_dense* A, const rsk_params* p, DensePlan* pl);
 
 // kernel = 0 and grid = 0: a tuned (kernel, grid) for this (dtype, m, n, eta), if the table has one
-// that applies to this matrix (alignment and leading dimension are not part of the key); else the
-// built-in choice.
+// that applies to this matrix; else the built-in choice. Ragged float32 rows have entries of their own (key
+// R = 1), as their launches are others than those of aligned rows of the same shape; without one
+// they take the shape's.
 template <typename T>
 int32_t plan_dense(const rsk_dense* A, const rsk_params* p, DensePlan* pl) {
   rsk_tune_entry e;
+  const bool rag = A->dtype == RSK_F32 && rows_ragged(A);
   if (p->kernel == 0 && p->grid == 0 &&
-      tune_find(RSK_TUNE_DENSE, A->dtype, A->m, A->n, p->eta, 0, &e) && e.v0 >= 1 && e.v0 <= 4 && e.v1 >= 1) {
+      ((rag && tune_find(RSK_TUNE_DENSE, A->dtype, A->m, A->n, p->eta, 1, &e)) ||
+       tune_find(RSK_TUNE_DENSE, A->dtype, A->m, A->n, p->eta, 0, &e)) && e.v0 >= 1 && e.v0 <= 4 && e.v1 >= 1) {
     rsk_params q = *p;
     q.kernel = (int32_t)e.v0;
     q.grid = (int32_t)e.v1;
