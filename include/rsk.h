@@ -478,7 +478,9 @@ int32_t rsk_plan_batched(int32_t nsys, int32_t dtype, const rsk_batch_item *item
  * left out is at most 2^-32 of a product, for operands of at least 2^-110 and
  * products of at least 2^-102; smaller ones lose low bits, and an infinite operand gives NaN),
  * 0 = a tuned choice (rsk_tune_*), else 3 when eta >= 128 and either R > 64 or
- * eta * n >= 3900000, else 1.
+ * the 64 x 64 tiles of A_tau X in splits of 128 columns, ceil(eta/64)
+ * ceil(R/64) ceil(n/128), are more than two a CU, else 1. (R > 64 with at most
+ * one such tile a CU runs 10-20% faster with kernel 1.)
  * Kernels 1 and 3 compute the same iteration with differently blocked sums
  * (equal to rounding).
  * Device faults and status_dev follow the single-RHS conventions (with kernel

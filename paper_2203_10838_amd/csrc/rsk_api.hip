@@ -515,13 +515,12 @@ int32_t solve_csr_t(const rsk_csr* A, const void* b, const rsk_params* p, void* 
   return e == hipSuccess ? RSK_OK : RSK_ERR_HIP;
 }
 
-constexpr int64_t kWideWork = 3900000;
 struct MultiPlan {
   int S, eta_pad, S2;
   int64_t kspan;
   int kernel;       // 1: step kernels (four per step), 2: one persistent launch for all K steps,
-                    // 3: the step kernels with wide product tiles (128 x 128, or 128 x 64 for R <= 64)
-  int tn;           // R edge of a product tile (64 or 128)
+                    // 3: the step kernels with wide product tiles (128 x tn)
+  int tn;           // R edge of a product tile: 64, or 128 for some wide tiles
   int tile;         // 64 (kernels 1, 2) or 128 (kernel 3): the tile edge of the products
   int pS;           // persistent launch: its split of the n columns (kspan rounded up to 64)
   int64_t pkspan;
@@ -538,25 +537,31 @@ int32_t plan_multirhs(const rsk_dense* A, int32_t R, const rsk_params* p, MultiP
   const int cus = device_cus() > 0 ? device_cus() : 256;
   rsk_tune_entry te;
   const bool tuned = tune_find(RSK_TUNE_MULTIRHS, A->dtype, A->m, A->n, p->eta, R, &te);
-  // the kernel: p->kernel 1, 2 or 3 as asked, else a tuned choice, else the wide-tile step kernels
-  // when eta fills at least one 128 tile and R does, or the step's rows are long and many enough that
-  // reading them (kWideWork elements) is what takes the time; else the 64 x 64 ones. Measured, us a
-  // step, 64 x 64 / wide (n, eta, R): 1000, 128, 96 22.9 / 21.2; 2048, 205, 256 26.9 / 27.5; 4096, 410,
-  // 256 43.1 / 35.4; 8192, 820, 256 104 / 69; 32768, 820, 256 375 / 214; with R = 64: 4096, 410 26.8 / 26.8;
-  // 6000, 601 32.2 / 32.5; 20000, 200 48.9 / 37.5; 8192, 820 44.0 / 37.1
-  pl->kernel = p->kernel >= 1 ? p->kernel
-             : (tuned && te.v2 >= 1 && te.v2 <= 3 ? (int)te.v2 : (p->eta >= 128 && (R > 64 || p->eta * A->n >= kWideWork) ? 3 : 1));
+  // the kernel: p->kernel 1, 2 or 3 as asked, else a tuned choice, else the wide-tile step kernels where eta
+  // fills at least one 128 tile and R does, or the 64 x 64 tiles of A_tau X, in splits of 128 columns, are more
+  // than two rounds on the CUs; else the 64 x 64 ones. Measured, us a step, 64 x 64 / wide, by n, eta, R (tiles),
+  // R = 64: 4096, 410 (224) 25.4 / 28.2; 8192, 410 (448) 30.2 / 31.0; 6000, 601 (470) 31.9 / 34.8; 32768, 128 (512) 37.4 /
+  // 38.8; 20000, 200 (628) 49.0 / 38.8; 12000, 400 (658) 46.0 / 39.3; 8192, 820 (832) 43.1 / 38.8 (20000, 128 (314) 35.9 /
+  // 32.7). R > 64: over two rounds 2048, 820, 192 (624) 40.9 / 36.3; 8192, 820, 256 (3328) 104 / 72; 32768, 820, 256 375 /
+  // 242; over one 4096, 200, 192 (384) 29.2 / 31.4; 8192, 128, 192 (384) 32.6 / 28.6; 2048, 820, 128 (416) 31.1 / 30.5; within
+  // one the 64 x 64 tiles would be the faster ones (1000, 128, 96 (32) 18.7 / 21.6; 2048, 205, 256 (256) 24.9 / 28.1; 8192,
+  // 128, 128 (256) 26.2 / 31.0): callers that rely on the choice by R ask for kernel 1 there, or tune
+  const int64_t units = (int64_t)((p->eta + 63) / 64) * ((R + 63) / 64) * ((A->n + 127) / 128);
+  const bool wide = p->eta >= 128 && (R > 64 || units > 2 * cus);
+  pl->kernel = p->kernel >= 1 ? p->kernel : (tuned && te.v2 >= 1 && te.v2 <= 3 ? (int)te.v2 : (wide ? 3 : 1));
   pl->tile = pl->kernel == 3 ? 128 : 64;
   pl->eta_pad = (p->eta + pl->tile - 1) / pl->tile * pl->tile;
   // the R edge of a product tile: wide tiles of 128 where they fill the device in splits of at least 256
-  // columns, else 64 (2048, 205, 256 27.5 us a step with 64, 29.4 with 128 and the device half empty)
+  // columns, else 64. Measured, us a step, with 64 / 128, n, eta, R: 6000, 150, 256 30.6 / 39.7; 8192, 128, 256 29.2 /
+  // 31.5; 12000, 200, 192 50.3 / 54.7; where 128 fills it: 8192, 820, 256 75.5 / 71.3; 20000, 400, 256 113 / 107; 32768, 820,
+  // 256 256 / 241 (12000, 400, 192 71.1 / 72.7)
   const int64_t most_s = (A->n + 255) / 256;
   const int tn = pl->tile == 128 && (R <= 64 || pl->eta_pad / 128 * ((R + 127) / 128) * most_s < cus) ? 64 : pl->tile;
   pl->tn = tn;
   const int tiles = (pl->eta_pad / pl->tile) * ((R + tn - 1) / tn);
   // about three 256-thread workgroups per CU for the n-long products, in whole XCD rounds (the
   // tiles of a split share one L2); or one 512-thread wide-tile workgroup per CU, rounded down (a
-  // second round on some CUs costs more than a few idle CUs or the L2 sharing)
+  // second round on some CUs costs more than a few idle CUs)
   int S = pl->tile == 128 ? cus / tiles : (3 * cus + tiles - 1) / tiles;
   if (S >= 8 && pl->tile != 128) S = (S + 7) / 8 * 8;
   if (tuned && te.v0 >= 1) S = (int)(te.v0 < 4096 ? te.v0 : 4096);
@@ -572,8 +577,16 @@ int32_t plan_multirhs(const rsk_dense* A, int32_t R, const rsk_params* p, MultiP
   if (tuned && te.v0 >= 1) max_s = (A->n + 63) / 64;
   if (S > max_s) S = (int)max_s;
   if (S < 1) S = 1;
-  pl->kspan = (A->n + S - 1) / S;
-  pl->kspan = (pl->kspan + 15) / 16 * 16;
+  const auto span_of = [&](int splits) { return ((A->n + splits - 1) / splits + 15) / 16 * 16; };
+  pl->kspan = span_of(S);
+  // wide tiles: whole XCD rounds below that where they make no workgroup's stages more (32 columns, in pairs).
+  // Measured, us a step, n, eta, R with 18 / 16 splits: 8192, 820, 256 74.6 / 72.3, 128 54.0 / 50.9, 4096, 820, 128 37.6 /
+  // 35.8; 36 / 32: 12000, 820, 64 51.4 / 48.5, 16384, 820, 128 78.2 / 73.8; 17 / 16: 6000, 601, 192 51.8 / 49.9; with more
+  // stages: 18 / 16, 12000, 820, 256 114.8 / 117.9, 32768, 820, 256 242.5 / 249.0; 63 / 55, 20000, 400, 128 74.4 / 78.2
+  if (pl->kernel == 3 && !(tuned && te.v0 >= 1) && S > 8 && S % 8 != 0) {
+    const int64_t span8 = span_of(S / 8 * 8);
+    if ((A->n + span8 - 1) / span8 % 8 == 0 && (span8 + 63) / 64 <= (pl->kspan + 63) / 64) pl->kspan = span8;
+  }
   pl->S = (int)((A->n + pl->kspan - 1) / pl->kspan);
   // the A_tau^T products write n x R: with fewer 64 x 64 tiles than CUs their sampled rows
   // are split over S2 workgroups (at least 64 rows each) and summed in a second kernel

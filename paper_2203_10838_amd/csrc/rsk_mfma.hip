@@ -495,8 +495,8 @@ __global__ void init_multirhs(float* Xs, float* X, size_t total, float lambda, i
 // Range: the split is exact for |a| >= 2^-110 and all its terms are normal numbers for |a b| >= 2^-102; terms
 // below 2^-126 are lost, so a sum below about 1e-29 in all loses bits that the float32 cores keep. An
 // infinite element gives NaN (a - a1).
-// Eight bfloat16 products take half of the time of one in float32. 32768 x 8192, R = 256, eta = 820: 78 us a
-// step (89 on the float32 cores, 70 with six terms).
+// Eight bfloat16 products take half of the time of one in float32. 32768 x 8192, R = 256, eta = 820, 16 splits:
+// 72 us a step (89 on the float32 cores, 65 with six terms).
 //
 // K advances 32 a stage. A thread loads 8 consecutive k of two columns (8 float2 loads, a wave one row's
 // 512 bytes; where k runs along memory, of two rows: 4 float4), splits them and writes the pieces as

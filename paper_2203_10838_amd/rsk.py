@@ -316,7 +316,8 @@ def solve_multirhs(A: torch.Tensor, B: torch.Tensor, *, lam: float, eta: int, al
     ``kernel``: 1 the step kernels, 2 one persistent launch for all K steps, 3 the step kernels with
     wide product tiles (float32 by three bfloat16 pieces, full precision for operands of at least
     2^-110 and products of at least 2^-102), 0 the library's choice (a tuned one, else 3 when
-    eta >= 128 and R > 64 or eta * n >= 3900000, else 1).
+    eta >= 128 and R > 64 or the 64 x 64 tiles of A_tau X in splits of 128 columns are more than two a CU, else 1;
+    R > 64 with at most one such tile a CU runs 10-20% faster with kernel 1).
 
     With ``ckpt`` (ceil(K/ckpt_every) x n x R float32) the x* checkpoints the
     adjoint recomputes from are written as well.
