@@ -223,6 +223,9 @@ int32_t rsk_spectral_norm2_dense(const rsk_dense *A, int64_t iters, void *v, dou
  * index outside [0, m)), RSK_ERR_ZERO_ROW (a block of zero rows: that step
  * leaves x* unchanged), RSK_ERR_NONFINITE. x* and x are bitwise reproducible
  * (y_out: see rsk_params).
+ * Workspace: the solve's, the relaxations and unit norms (K + m elements), and
+ * 32 KiB for the Gram matrix of each step of a chunk (float64: of each 2560 columns
+ * of it), 64 MiB in all at most (more only for n above 5 million).
  */
 int32_t rsk_workspace_size_bsk_dense(const rsk_dense *A, const rsk_params *p, size_t *bytes);
 int32_t rsk_bsk_solve_dense(const rsk_dense *A, const void *b, const rsk_params *p, void *x_star, void *x,

@@ -131,9 +131,8 @@ using rsk::kOneHopWords;
 // is faster (20000 columns, eta = 96 ... 256: 4-7% shorter steps)
 constexpr int kRtTwoGroupMinEta = 88, kRtTwoGroupMaxEta = 800;
 constexpr int kRtPfBytes = 147456;
-// (256 workgroups of 20000 columns, us a step without / with LO, 1 us less each since the column sums
-// read words: eta = 16 7.4 / 6.9, 64 6.7 / 6.5, 96
-// 7.2 / 7.2, 128 7.6 / 7.7)
+// rows up to which a step takes the form for small steps whatever its owners (256 workgroups of 20000 columns, us a
+// step without / with it: eta = 16 5.9 / 5.4, 64 5.9 / 5.6, 96 6.4 / 6.3, 128 6.8 / 6.7; 10000 columns, 256 6.4 / 6.7)
 constexpr int kRtSmallEta = 95;
 // largest eta of the 1024-thread form
 constexpr int kRtWideEta = 768;
@@ -256,10 +255,9 @@ bool plan_dense_rt(const rsk_dense* A, const rsk_params* p, int rg, DensePlan* p
   const int rp = (etaR + rpp - 1) / rpp;
   // one hop while every wave reduces at most one row of few partials (each row more costs a
   // serial poll, sum and division)
-  int two_hop = (int64_t)C * etaR > rsk::kRtSoloOneHopWords || etaR > nt / 64;
+  const int two_hop = (int64_t)C * etaR > rsk::kRtSoloOneHopWords || etaR > nt / 64;
   // each wave reduces at most kRtOwnMax rows per step
   const int own = rsk::kRtOwnMax * (nt / 64);
-  if (!two_hop && etaR > own) two_hop = 1;
   if (two_hop && (etaR + C - 1) / C > own) return false;
   // small steps (LO): several rows a wave, or at most kRtSmallEta rows, the whole next tile in LDS
   const bool lo = rg == 1 && nt == 1024 && rp * cpl <= kRtPfBytes / (nt * 16) &&

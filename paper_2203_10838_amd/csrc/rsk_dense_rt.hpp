@@ -84,6 +84,9 @@ __device__ __forceinline__ void rt_run(const DenseArgs<float>& a, const int g, c
   constexpr int kOwners = kRtWaves / 2;
   constexpr int kOwnMax = kRtOwnMax * kRtWaves / kOwners;
   static_assert(64 * kOwners == kBrtOneHopRows, "one hop: a row an owner thread");
+  // A form of this step for 256 threads, two workgroups a CU, with the systems' descriptors in scalar registers did not
+  // finish a test, and reading it did not show why: another thread count needs that answered first.
+  static_assert(NT == 512, "one 512-thread workgroup a CU; a 256-thread form hung for a cause not found");
   static_assert(SW <= NT, "the slice's columns, one a thread");
   __shared__ float4 xs4[CL * CPL];                // x* slice
   __shared__ float4 xv4[CL * CPL];                // x slice

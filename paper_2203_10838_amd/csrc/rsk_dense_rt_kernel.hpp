@@ -117,11 +117,10 @@ __global__ __launch_bounds__(NT) void rska_dense_rt(DenseArgs<float> a) {
   // needs the whole exchange to hide it, and is issued right after the dots.
   constexpr bool kPfAfterHop1 = kHbmSlots == 0;
   // LO: the steps whose length is a chain of latencies (many rows a wave, or few rows). A wave that
-  // reduces several rows fetched their b and norms in branches, an index and a value round trip a
-  // row: 3 us of a step of 64 rows. With LO lane j fetches row j of its wave, all rows at once, from
-  // indices loaded a step earlier (n = 500, eta = 64: 8.1 -> 4.5 us a step, 3.5 with the column sums' words, together with the second
-  // hop; eta = 256 5.1 -> 4.7; n = 20000, eta = 16 7.4 -> 6.9). Other steps hide the branch's wait
-  // and keep it: n = 10000, eta = 256 7.2 us a step against 7.5 with LO.
+  // reduces several rows fetches their b and norms in branches, an index and a value round trip a
+  // row; with LO lane j fetches row j of its wave, all rows at once, from indices loaded a step
+  // earlier. us a step without / with it: n = 500, eta = 64 3.9 / 3.6, 256 4.4 / 4.0; n = 2000, 64 4.3 / 3.9; n = 20000,
+  // 16 5.9 / 5.4. Other steps hide the branch's wait and keep it: n = 10000, eta = 256 6.4 / 6.7.
   static_assert(!LO || (RG == 1 && kHbmSlots == 0), "lane-owned rows: one group, the whole next tile in LDS");
   __shared__ float4 pf[NPF > 0 ? NPF * NT : 1];
   __shared__ int nrow[PL > 0 ? PL * kRtRowsPerPass : 1];  // rows of the passes holding prefetched slots
