@@ -196,9 +196,9 @@ __global__ __launch_bounds__(kDenseThreads, 2) void rska_batched(const rsk_batch
     DenseArgs<T> a;
     fill_args(a, it, pl, region);
     if (a.tile_cache == 2 && dense_pipe_ok(sizeof(T), VEC, a.eta, a.wq_max))
-      dense_run<T, VEC, kDenseThreads, true>(a, rank, rank, smem);
+      dense_run<T, VEC, kDenseThreads, true, false>(a, rank, rank, smem);
     else
-      dense_run<T, VEC, kDenseThreads, false>(a, rank, rank, smem);
+      dense_run<T, VEC, kDenseThreads, false, false>(a, rank, rank, smem);
   }
 }
 

@@ -24,9 +24,9 @@ template <typename T, int VEC, int NT>
 __global__ __launch_bounds__(NT, 2) void rska_dense_persistent(DenseArgs<T> a) {
   extern __shared__ __align__(16) unsigned char smem[];
   if (a.tile_cache == 2 && dense_pipe_ok(sizeof(T), VEC, a.eta, a.wq_max))
-    dense_run<T, VEC, NT, true>(a, blockIdx.x, xcd_slice(blockIdx.x, a.G), smem);
+    dense_run<T, VEC, NT, true, true>(a, blockIdx.x, xcd_slice(blockIdx.x, a.G), smem);
   else
-    dense_run<T, VEC, NT, false>(a, blockIdx.x, xcd_slice(blockIdx.x, a.G), smem);
+    dense_run<T, VEC, NT, false, true>(a, blockIdx.x, xcd_slice(blockIdx.x, a.G), smem);
 }
 
 template <typename T>
